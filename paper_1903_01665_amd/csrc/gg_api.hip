@@ -554,6 +554,8 @@ int plan_make(gg_graph g, gg_ws ws, int algo, int source, const int* sources_dev
     const long long n = g->n;
     const long long ntiles = (n + 63) / 64;
     const long long ngroups = (ntiles + 63) / 64;
+    R.item_shift = item_shift_for(ntiles);
+    const long long nitems = ngroups << (6 - R.item_shift);
     const int nh = p.cc ? g->n_shchunks : g->n_hchunks;
     p.g_init = grid((n + kBlock - 1) / kBlock);
     p.g_seed = grid((nsrc + kBlock - 1) / kBlock);
@@ -564,20 +566,22 @@ int plan_make(gg_graph g, gg_ws ws, int algo, int source, const int* sources_dev
     } else if (!p.async && p.edge) {
         p.g_round = grid((g->m / 4 + kBlock - 1) / kBlock);
     } else if (diropt && p.cc) {
-        p.g_round = grid(std::max(ngroups * kParts / wpb + 1, (g->m / 4 + kBlock - 1) / kBlock));
+        p.g_round = grid(std::max(nitems / wpb + 1, (g->m / 4 + kBlock - 1) / kBlock));
     } else if (diropt && algo == GG_ALGO_SSSP) {
-        p.g_round = grid(std::max(ngroups * kParts, ntiles + g->n_tchunks) / wpb + 1);
+        p.g_round = grid(std::max(nitems, ntiles + g->n_tchunks) / wpb + 1);
     } else if (diropt) {
-        p.g_round = grid(std::max(ngroups * kParts, ntiles) / wpb + 1);
+        p.g_round = grid(std::max(nitems, ntiles) / wpb + 1);
     } else if (uf) {
         p.g_round = grid((n + kBlock - 1) / kBlock);
     } else {
-        p.g_round = grid((ngroups * kParts + wpb - 1) / wpb);
+        p.g_round = grid((nitems + wpb - 1) / wpb);
     }
     p.need_heavy = p.async && (p.edge || diropt || o.mapping == GG_MAP_BALANCED) && nh > 0;
     // the heavy kernel of an SSSP pull round clears the frontier it read
     if (diropt && algo == GG_ALGO_SSSP) p.need_heavy = true;
-    p.g_heavy = grid((nh + 64LL * wpb - 1) / (64LL * wpb));
+    // about kHeavyPerWave chunks a wavefront (their rows are checked with one
+    // load of the wavefront, the marked ones served one after another)
+    p.g_heavy = grid((nh + (long long)kHeavyPerWave * wpb - 1) / ((long long)kHeavyPerWave * wpb));
     if (diropt && algo == GG_ALGO_SSSP)  // enough blocks to clear the flags quickly
         p.g_heavy = std::max(p.g_heavy, grid((ngroups * 256 + kBlock - 1) / kBlock));
     p.need_jump = p.cc && p.edge && (!p.async || diropt) && R.jump && !uf;
@@ -960,6 +964,7 @@ int gg_graph_upload(int32_t n, int64_t m, const int32_t* row_ptr, const int32_t*
     g->argmax_deg = argmax_deg;
     g->heavy = (double)max_deg >= 128.0 * ((double)m / (double)n) && m > 0 ? kHeavySkewed
                                                                             : kHeavyUniform;
+    g->chunk = chunk_for(m);
     g->weighted = w != nullptr;
     if (!on_dev && w && m > 0) {
         g->max_w = hc.max_w;

@@ -18,10 +18,36 @@ constexpr int kMaxStatBlocks = 4096; // per-block statistics slots
 // graph it cuts short rows into underfilled chunks)
 constexpr int kHeavySkewed = 16;
 constexpr int kHeavyUniform = 32;
-constexpr int kChunk = 512;          // edges per heavy-row chunk
+constexpr int kChunk = 512;          // most edges per heavy-row chunk
 constexpr int kKinds = 3;            // statistics kinds: round, heavy chunks, auxiliary
-constexpr int kParts = 8;            // frontier work items per 64-tile group (8 tiles each)
+constexpr int kItemTiles = 8;        // most tiles of a frontier work item
+constexpr int kFillWaves = 8192;     // wavefronts that fill the device (256 CUs x 32)
 constexpr int kXcd = 8;              // accelerator dies; workgroups go to them round-robin
+// Tiles per frontier work item, as a shift: the most (up to kItemTiles) that
+// still leave an item for each of kFillWaves wavefronts.  Graphs of 4M
+// vertices and more fill the device with 8-tile items, the best size measured
+// there; on an R-MAT graph of 2^18 vertices 8-tile items kept 512 wavefronts
+// busy and a dense worklist round took 106 us, with one-tile items 25 us.
+inline int item_shift_for(long long ntiles) {
+    int sh = 0;
+    while ((2 << sh) <= kItemTiles && (ntiles >> (sh + 1)) >= kFillWaves) ++sh;
+    return sh;
+}
+
+// Edges per heavy-row chunk: the least power of two from 128 that cuts the
+// graph into at most four chunks for each of kFillWaves wavefronts (512 from
+// 2^25 edges on, the best size measured there).  With 512-edge chunks and 64
+// chunks a wavefront the dense chunk rounds of an R-MAT graph of 2^22 edges
+// took 148 and 97 us (132 blocks); with 128-edge chunks, four a wavefront, 84
+// and 73 us: what is left there is the rate of its atomics (27 G/s at most on
+// this device, about 8 G/s on skewed heads, whatever the scope; plain loads
+// and stores run at 60-400 G/s).
+inline int chunk_for(long long m) {
+    int c = 128;
+    while (c < kChunk && m / c > 4 * kFillWaves) c *= 2;
+    return c;
+}
+
 enum Kind { KIND_ROUND = 0, KIND_HEAVY = 1, KIND_AUX = 2 };
 
 enum Algo { SSSP = 0, BFS = 1, CC = 2 };
@@ -122,6 +148,7 @@ struct Round {
                     // CC: the both-directions rows) instead of pushing or sweeping
     int direct_lists; // SSSP local expansion: list passes issue their atomics without a
                       // check load of the head value
+    int item_shift; // log2 of the tiles of a frontier work item
     int* rmin;      // CC on a renumbered graph: per-label minimum of the caller's ids,
                     // filled with INT_MAX by the init kernel (null otherwise)
 };

@@ -32,11 +32,19 @@
 
 namespace gg {
 
-// A frontier work item is one kParts-th of a 64-tile group: the wavefront
-// checks the tile flags of its part (64 / kParts tiles) and serves the
-// flagged ones.  Fewer, larger items make the scan of a sparse frontier
-// cheaper (deep graphs run thousands of rounds with small frontiers) at the
-// price of balance on dense ones; 8 tiles per item measured best.
+// A frontier work item is 2^item_shift consecutive tiles (1 to kItemTiles; 64
+// tiles make a group): the wavefront checks their flags and serves the flagged
+// ones.  Larger items make the scan of a sparse frontier cheaper (deep graphs
+// run thousands of rounds with small frontiers) at the price of balance on
+// dense ones; item_shift_for (gg_internal.h) states the rule.
+
+// Round kernels that run 2048 blocks (eight per CU): at most 80 scalar
+// registers.  A wavefront with more is allocated 96 of them and 16 for the
+// trap handler, only seven fit a SIMD, and the last 256 blocks run in a second
+// wave (the BFS pull rounds of a 3.0M-vertex R-MAT graph: 29 and 19 us with 80
+// registers, 38 and 29 us with 82).
+#define GG_ROUND_KERNEL(waves) \
+    __global__ __launch_bounds__(256, waves) __attribute__((amdgpu_num_sgpr(80)))
 
 // Edges each lane keeps in flight in the relaxation loops.
 constexpr int kBatch = 4;
@@ -936,14 +944,14 @@ __device__ void cc_first_pass(const Round& R, Acc& acc) {
         }
         __builtin_amdgcn_wave_barrier();
     }
-    // Heavy rows, chunk by chunk (kChunk edges, the chunk size of every
-    // graph).  The loop is pipelined across a wavefront's chunks: the next
-    // chunk's descriptor and row end are fetched while this chunk's columns
-    // load; the column loads of a chunk are issued together and need only
-    // the chunk's first edge (indices clamped to the column array, lanes
-    // past the row end masked after the load); and the result of a chunk's
-    // atomicMin (did it lower the label: push the row) is read one chunk
-    // later, so that the atomic's round trip overlaps the next chunk's loads.
+    // Heavy rows, chunk by chunk (at most kChunk edges).  The loop is
+    // pipelined across a wavefront's chunks: the next chunk's descriptor and
+    // row end are fetched while this chunk's columns load; the column loads of
+    // a chunk are issued together and need only the chunk's first edge
+    // (indices clamped to the column array, lanes past the chunk's end masked
+    // after the load); and the result of a chunk's atomicMin (did it lower the
+    // label: push the row) is read one chunk later, so that the atomic's round
+    // trip overlaps the next chunk's loads.
     constexpr int C = kChunk / 64;
     const long long nch = g.n_shchunks;
     const int last = g.ms - 1;
@@ -957,7 +965,7 @@ __device__ void cc_first_pass(const Round& R, Acc& acc) {
         int v[C];
 #pragma unroll
         for (int j = 0; j < C; ++j) v[j] = g.scol[min(c.y + j * 64 + lane, last)];
-        const int e1 = min(c.y + kChunk, rend);
+        const int e1 = min(c.y + g.chunk, rend);
         int x = kInf;
 #pragma unroll
         for (int j = 0; j < C; ++j)
@@ -1050,15 +1058,15 @@ __device__ __forceinline__ void vasync_packed(const Round& R, Acc& acc, bool nf,
     const long long gw = (long long)blockIdx.x * wpb + (threadIdx.x >> 6);
     const long long tw = (long long)gridDim.x * wpb;
     const long long ntiles = (n + 63) / 64;
-    const long long nitems = (ntiles + 63) / 64 * kParts;
+    const long long nitems = ((ntiles + 63) / 64) << (6 - R.item_shift);
     __shared__ int s_pend[4][64];  // blocks of 256 threads: four wavefronts
     int* pend = s_pend[threadIdx.x >> 6];
     int np = 0;  // vertices in the list (the same in every lane)
     for (long long it = gw; it < nitems; it += tw) {
-        const long long st = it / kParts;
-        const int part = (int)(it % kParts);
+        const long long st = it >> (6 - R.item_shift);
+        const int part = (int)(it & ((64 >> R.item_shift) - 1));
         const long long t = st * 64 + lane;
-        const bool mine = lane / (64 / kParts) == part;
+        const bool mine = (lane >> R.item_shift) == part;
         const bool tfl = mine && t < ntiles && tf[t] != 0;
         unsigned long long tm = __ballot(tfl);
         if (tfl) tf[t] = 0;
@@ -1099,12 +1107,12 @@ __device__ __forceinline__ void vasync_body(const Round& R, Acc& acc, bool nf, i
     const long long gw = (long long)blockIdx.x * wpb + (threadIdx.x >> 6);
     const long long tw = (long long)gridDim.x * wpb;
     const long long ntiles = (n + 63) / 64;
-    const long long nitems = (ntiles + 63) / 64 * kParts;
+    const long long nitems = ((ntiles + 63) / 64) << (6 - R.item_shift);
     for (long long it = gw; it < nitems; it += tw) {
-        const long long st = it / kParts;
-        const int part = (int)(it % kParts);
+        const long long st = it >> (6 - R.item_shift);
+        const int part = (int)(it & ((64 >> R.item_shift) - 1));
         const long long t = st * 64 + lane;
-        const bool mine = lane / (64 / kParts) == part;
+        const bool mine = (lane >> R.item_shift) == part;
         const bool tfl = mine && t < ntiles && tf[t] != 0;
         unsigned long long tm = __ballot(tfl);
         if (tfl) tf[t] = 0;
@@ -1163,7 +1171,7 @@ __device__ __forceinline__ void vasync_body(const Round& R, Acc& acc, bool nf, i
 // NF: the near-far schedule (SSSP, balanced mapping, R.delta > 0); a
 // separate instantiation keeps its bookkeeping out of the plain rounds.
 template <int A, int MAP, bool NF = false>
-__global__ __launch_bounds__(256) void k_vasync(Round R) {
+GG_ROUND_KERNEL(NF ? 6 : 8) void k_vasync(Round R) {
     if (!round_begin(R)) return;
     clear_prev_heavy(R);
     const bool nf = NF;
@@ -1258,17 +1266,17 @@ __device__ __forceinline__ void vasync_local(const Round& R, Acc& acc, bool nf, 
     const long long gw = (long long)blockIdx.x * wpb + (threadIdx.x >> 6);
     const long long tw = (long long)gridDim.x * wpb;
     const long long ntiles = (n + 63) / 64;
-    const long long nitems = (ntiles + 63) / 64 * kParts;
+    const long long nitems = ((ntiles + 63) / 64) << (6 - R.item_shift);
     __shared__ int s_pend[4][64];  // blocks of 256 threads: four wavefronts
     __shared__ int4 s_loc[4][2 * kLocalCap];
     int* pend = s_pend[threadIdx.x >> 6];
     int4* lb = s_loc[threadIdx.x >> 6];
     int np = 0;
     for (long long it = gw; it < nitems; it += tw) {
-        const long long st = it / kParts;
-        const int part = (int)(it % kParts);
+        const long long st = it >> (6 - R.item_shift);
+        const int part = (int)(it & ((64 >> R.item_shift) - 1));
         const long long t = st * 64 + lane;
-        const bool mine = lane / (64 / kParts) == part;
+        const bool mine = (lane >> R.item_shift) == part;
         const bool tfl = mine && t < ntiles && tf[t] != 0;
         unsigned long long tm = __ballot(tfl);
         if (tfl) tf[t] = 0;
@@ -1311,7 +1319,7 @@ __global__ __launch_bounds__(256, 6) void k_vlocal(Round R) {
 // edge list) and relaxes the edges whose source is on the frontier.  Runs of
 // light rows are walked; heavy flagged rows go to the chunk queue.
 template <int A>
-__global__ __launch_bounds__(256) void k_easync(Round R) {
+GG_ROUND_KERNEL(8) void k_easync(Round R) {
     if (!round_begin(R)) return;
     clear_prev_heavy(R);
     const DevGraph& g = R.g;
@@ -1327,13 +1335,13 @@ __global__ __launch_bounds__(256) void k_easync(Round R) {
     const long long gw = (long long)blockIdx.x * wpb + (threadIdx.x >> 6);
     const long long tw = (long long)gridDim.x * wpb;
     const long long ntiles = (n + 63) / 64;
-    const long long nitems = (ntiles + 63) / 64 * kParts;
+    const long long nitems = ((ntiles + 63) / 64) << (6 - R.item_shift);
     Acc acc;
     for (long long it = gw; it < nitems; it += tw) {
-        const long long st = it / kParts;
-        const int part = (int)(it % kParts);
+        const long long st = it >> (6 - R.item_shift);
+        const int part = (int)(it & ((64 >> R.item_shift) - 1));
         const long long t = st * 64 + lane;
-        const bool mine = lane / (64 / kParts) == part;
+        const bool mine = (lane >> R.item_shift) == part;
         const bool tfl = mine && t < ntiles && tf[t] != 0;
         unsigned long long tm = __ballot(tfl);
         if (tfl) tf[t] = 0;
@@ -1399,7 +1407,7 @@ __global__ __launch_bounds__(256) void k_easync(Round R) {
 // level r+1 at the first one on level r, so no atomics and few edges.  The
 // frontier size is the sum of the previous round's per-block push counts;
 // every block computes the same sum, so the direction is grid-uniform.
-__global__ __launch_bounds__(256) void k_bfs_diropt(Round R) {
+GG_ROUND_KERNEL(8) void k_bfs_diropt(Round R) {
     if (!round_begin(R)) return;
     clear_prev_heavy(R);
     const DevGraph& g = R.g;
@@ -1614,7 +1622,7 @@ __device__ void pull_round(const Round& R, Acc& acc) {
     // heavy rows, one chunk per wavefront step: kBatch edges per lane
     for (long long k = gw; k < nch; k += tw) {
         const int2 c = ich[k];
-        const int e1 = min(c.y + kChunk, irow[c.x + 1]);
+        const int e1 = min(c.y + g.chunk, irow[c.x + 1]);
         int u[kChunk / 64], wt[kChunk / 64];
 #pragma unroll
         for (int j = 0; j < kChunk / 64; ++j) {
@@ -1640,7 +1648,7 @@ __device__ void pull_round(const Round& R, Acc& acc) {
 // vertex over its in-edges (the innbrs iterator) when the frontier's
 // out-edges are a large part of the graph: a pull round needs no atomics on
 // light rows and reads each in-edge's tail flag before its value.
-__global__ __launch_bounds__(256) void k_sssp_diropt(Round R) {
+GG_ROUND_KERNEL(8) void k_sssp_diropt(Round R) {
     if (!round_begin(R)) return;
     clear_prev_heavy(R);
     Ctl* ctl = R.ws.ctl;
@@ -1708,7 +1716,7 @@ __global__ __launch_bounds__(256) void k_heavy(Round R) {
         // expansion (levels differ within a round) the row's own level,
         // lowered atomically.
         const bool lvl = A == BFS && R.hops == 0;
-        const int cend = on ? min(c.y + kChunk, row[c.x + 1]) : 0;
+        const int cend = on ? min(c.y + g.chunk, row[c.x + 1]) : 0;
         unsigned long long am = __ballot(on);
         while (am) {
             const int o = __ffsll(am) - 1;
@@ -1762,7 +1770,7 @@ __global__ __launch_bounds__(256) void k_jump(Round R) {
 // from the both-directions CSR.  A sweep puts every vertex it lowers on the
 // next frontier (so a later worklist round sees every vertex whose value
 // changed after its edges were last read) and clears the frontier it skips.
-__global__ __launch_bounds__(256) void k_cc_diropt(Round R) {
+GG_ROUND_KERNEL(8) void k_cc_diropt(Round R) {
     if (!round_begin(R)) return;
     clear_prev_heavy(R);
     Ctl* ctl = R.ws.ctl;

@@ -19,6 +19,7 @@ namespace gg {
 
 constexpr int kVersion = 1;
 constexpr int kBlock = 256;
+constexpr int kHeavyPerWave = 4;  // heavy-row chunks a wavefront of the chunk kernel checks
 constexpr int kMaxBatch = 16;
 constexpr int kDefaultTimeLimitMs = 60000;
 
