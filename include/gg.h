@@ -209,6 +209,12 @@ typedef struct {
 #define GG_OPT_LISTS_DIRECT 8u
 
 /* Statistics of the last traversal run on a workspace. */
+/* A small graph (up to 32,768 vertices; up to 65,536 edges, BFS 32,768) whose
+ * call leaves mode, schedule, mapping and time limit to the library, and an
+ * instance of a batch of up to 32,768 vertices and 131,072 edges, is traversed
+ * by one workgroup in one launch: the variant reported is then the one AUTO
+ * resolves to, iterations counts that launch's own rounds, and block_threads
+ * is 1024. */
 typedef struct {
     int32_t algo, mode, sched, mapping; /* the variant that ran (AUTO resolved) */
     int32_t status;                     /* device-side gg_status of that run */
@@ -466,7 +472,9 @@ int gg_graph_class(gg_graph g, int32_t* size_class, int32_t* skew_class, int32_t
  * and graph class (gg_class_of) are concatenated into one graph with
  * per-instance vertex offsets, so every instance is a separate component
  * and one multi-source traversal of the group computes all of them exactly
- * as separate calls would (bit-identical).  Each group runs in the variant
+ * as separate calls would (bit-identical).  Instances small enough for one
+ * workgroup each (see gg_stats) form one group per algorithm, one launch for
+ * all of them.  Each other group runs in the variant
  * the tuner picks for the group's graph (a near-far pick runs as the plain
  * worklist: the buckets pay off on large single-source traversals, not on a
  * group of small ones), on a stream of its own; after the

@@ -366,6 +366,7 @@ void free_graph_arrays(gg_graph g) {
     dfree(g->oldid);
     dfree(g->eorig);
     dfree(g->epos);
+    dfree(g->inst);
     g->srow = g->scol = g->ssrc = nullptr;
 }
 
@@ -476,6 +477,19 @@ void resolve(gg_graph g, int algo, const gg_opts* in, gg_opts* out) {
     *out = o;
 }
 
+// Whether a call runs as one workgroup: every variant field and the time limit
+// left to the library (a launch cannot be stopped half-way), and a graph below
+// the sizes up to which one workgroup is faster; or a group of a batch made so.
+bool whole_ok(gg_graph g, int algo, int nsrc, const gg_opts* in) {
+    if (nsrc > 0) return g->inst != nullptr;
+    if (in && (in->mode == GG_VERTEX || in->mode == GG_EDGE ||
+               (in->sched >= GG_SYNC && in->sched <= GG_UNIONFIND && in->sched != GG_SCHED_AUTO) ||
+               (in->mapping >= GG_MAP_THREAD && in->mapping <= GG_MAP_BALANCED) ||
+               in->time_limit_ms > 0))
+        return false;
+    return g->n <= kSmallN && g->m <= small_max_edges(algo);
+}
+
 }  // namespace
 
 namespace gg {
@@ -550,6 +564,12 @@ int plan_make(gg_graph g, gg_ws ws, int algo, int source, const int* sources_dev
                      : (o.flags & GG_OPT_LISTS_CHECKED) ? 0
                                                          : (g->levels >= 256 ? 1 : 0);
 
+    if (whole_ok(g, algo, nsrc, opts)) {
+        p.whole = true;
+        p.g_round = nsrc > 0 ? std::min(nsrc, kMaxStatBlocks) : 1;
+        R.inst = nsrc > 0 ? g->inst : nullptr;
+        return GG_OK;
+    }
     const int wpb = kBlock / 64;
     const long long n = g->n;
     const long long ntiles = (n + 63) / 64;
@@ -629,6 +649,9 @@ hipError_t plan_launch(Plan& p, int kind, F&& fn) {
 }
 
 hipError_t plan_init(Plan& p) {
+    if (p.whole)
+        return p.R.inst ? plan_launch(p, KIND_AUX, [&] { return launch_small_begin(p.R, p.s); })
+                        : hipSuccess;
     hipError_t e = plan_launch(p, KIND_AUX, [&] {
         return launch_init(p.R, p.algo, p.async, p.g_init, kBlock, p.s);
     });
@@ -641,6 +664,13 @@ hipError_t plan_init(Plan& p) {
 hipError_t plan_round(Plan& p, int r) {
     Round& R = p.R;
     R.r = r;
+    if (p.whole) {
+        if (r > 0) return hipSuccess;
+        const int max_n = R.inst ? p.g->inst_max_n : p.g->n;
+        const long long max_m = R.inst ? p.g->inst_max_m : p.g->m;
+        return plan_launch(p, KIND_ROUND,
+                           [&] { return launch_small(R, p.algo, max_n, max_m, p.s); });
+    }
     hipError_t e = plan_launch(p, KIND_ROUND, [&] {
         if (p.uf) return launch_uf(R, p.g_round, kBlock, p.s);
         if (p.diropt && p.cc) return launch_cc_diropt(R, p.g_round, kBlock, p.s);
@@ -713,6 +743,7 @@ int reserve_stamps(gg_ws ws, hipStream_t s, long long span, hipError_t* err) {
 // rounds suffice; a near-far round may only raise the bound, which happens
 // at most (largest possible distance) / delta times.
 long long max_rounds(const Plan& p) {
+    if (p.whole) return 1;
     long long r = (long long)p.g->n + 2;
     if (p.R.delta > 0)
         r += std::min<long long>(((long long)p.g->n * p.g->max_w) / p.R.delta + 1, 1LL << 29);
@@ -732,11 +763,13 @@ int drive_start(Drive& d, long long r0, int stamp_base, int tag) {
     d.stopping = false;
     d.finishing = false;
     d.fin_seq = 0;
-    // two batches in flight from the start
-    for (int i = 0; i < 2; ++i) {
+    // two batches in flight from the start (a whole traversal is one launch:
+    // its batch stands as the older of the two)
+    for (int i = 0; i < (d.p.whole ? 1 : 2); ++i) {
         int rc = drive_enqueue(d);
         if (rc != GG_OK) return rc;
     }
+    if (d.p.whole) d.k = 2;
     return GG_OK;
 }
 
@@ -800,9 +833,11 @@ int drive_step(Drive& d, bool block) {
     auto completed = [&](int slot) { return __atomic_load_n(prog_word(ws), __ATOMIC_ACQUIRE) >= d.seq[slot]; };
     // batch k-2 is the older of the two outstanding (k-1 the newer one)
     if (d.poll) {
-        if (reported()) {
+        if (reported() && !p.whole) {
             // the values are final once the end is found; rounds still queued
-            // return at their first instruction
+            // return at their first instruction.  (A whole traversal reports
+            // from the kernel that writes the values: its batch's marker
+            // must have run.)
             return drive_end(d, block);
         }
         if (d.stopping) {
@@ -865,7 +900,8 @@ void record_last(Plan& p, int status, long long rounds) {
     ws->last.mapping = p.edge ? 0 : p.o.mapping;
     ws->last.status = status;
     ws->last.grid_blocks = p.g_round;
-    ws->last.block_threads = kBlock;
+    ws->last.block_threads = p.whole ? kSmallBlock : kBlock;
+    ws->small_blocks = p.whole ? p.g_round : 0;
 }
 
 int run_multi(gg_graph g, gg_ws ws, int algo, int source, const int* sources_dev, int nsrc,
@@ -1242,6 +1278,7 @@ int gg_last_stats(gg_graph g, gg_ws ws, gg_stats* out) {
                         hipMemcpyDeviceToHost));
     gg_stats s = ws->last;
     s.iterations = c.done ? c.iters : -1;
+    if (ws->small_blocks > 0) st.resize((size_t)ws->small_blocks);  // the slots it wrote
     for (const Stat& x : st) {
         s.edges_processed += x.edges;
         s.vertices_processed += x.verts;
@@ -1279,8 +1316,8 @@ int gg_last_profile(gg_graph g, gg_ws ws, gg_profile* out) {
         k.launches++;
         k.total_ms += ms;
     }
-    for (int kind = 0; kind < kKinds; ++kind)
-        for (int b = 0; b < kMaxStatBlocks; ++b) {
+    for (int kind = 0; kind < (ws->small_blocks > 0 ? 1 : kKinds); ++kind)
+        for (int b = 0; b < (ws->small_blocks > 0 ? ws->small_blocks : kMaxStatBlocks); ++b) {
             const Stat& x = st[(size_t)kind * kMaxStatBlocks + b];
             out->kind[kind].edges_processed += x.edges;
             out->kind[kind].vertices_processed += x.verts;

@@ -70,6 +70,10 @@ bool valid_instance(const gg_instance& x, int* max_deg) {
     return true;
 }
 
+bool fits_workgroup(const gg_instance& x) {
+    return x.n <= kSmallN && x.m <= kSmallM;
+}
+
 void destroy_group(Group& G) {
     if (G.stream) (void)hipStreamSynchronize(G.stream);
     if (G.exec) (void)hipGraphExecDestroy(G.exec);
@@ -125,7 +129,9 @@ int gg_batch_create(const gg_instance* inst, int32_t count, uint32_t flags, void
     *out = nullptr;
     if (!inst || count < 1) return GG_EINVAL;
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-    // group key: algorithm and graph class (size, skew) of the instance
+    // group key: algorithm and graph class (size, skew) of the instance; the
+    // instances that fit a workgroup form one group per algorithm, which runs
+    // as one launch with a workgroup each
     std::map<std::tuple<int, int, int>, std::vector<int>> keys;
     for (int i = 0; i < count; ++i) {
         int md = 0;
@@ -133,6 +139,7 @@ int gg_batch_create(const gg_instance* inst, int32_t count, uint32_t flags, void
         int32_t sc = 0, kc = 0, dc = 0;
         gg_class_of(inst[i].m, inst[i].n, md, -1, &sc, &kc, &dc);
         if (flags & GG_BATCH_ONE_GROUP) sc = kc = 0;
+        else if (fits_workgroup(inst[i])) sc = kc = -1;
         keys[std::make_tuple(inst[i].algo, sc, kc)].push_back(i);
     }
     gg_batch b = new (std::nothrow) gg_batch_s();
@@ -193,6 +200,25 @@ int gg_batch_create(const gg_instance* inst, int32_t count, uint32_t flags, void
             hipEventCreateWithFlags(&G.done, hipEventDisableTiming) != hipSuccess ||
             hipHostMalloc(reinterpret_cast<void**>(&G.h_ctl), 2 * sizeof(int)) != hipSuccess)
             return bail(GG_EHIP);
+        bool fit = true;
+        int max_n = 0;
+        long long max_m = 0;
+        for (int i : G.members) {
+            fit = fit && fits_workgroup(inst[i]);
+            max_n = std::max(max_n, inst[i].n);
+            max_m = std::max<long long>(max_m, inst[i].m);
+        }
+        if (fit) {
+            std::vector<int> first(G.vbase.begin(), G.vbase.end());
+            first.push_back((int)G.n);
+            if (dalloc(&G.g->inst, first.size()) != hipSuccess ||
+                hipMemcpyAsync(G.g->inst, first.data(), sizeof(int) * first.size(),
+                               hipMemcpyHostToDevice, s) != hipSuccess ||
+                hipStreamSynchronize(s) != hipSuccess)
+                return bail(GG_EHIP);
+            G.g->inst_max_n = max_n;
+            G.g->inst_max_m = max_m;
+        }
         gg_resolve(G.g, G.algo, nullptr, &G.opts);
         // The table's choice is measured on single-source traversals.  A
         // group is one traversal from hundreds of sources over as many small

@@ -48,6 +48,28 @@ inline int chunk_for(long long m) {
     return c;
 }
 
+// Whole traversals in one workgroup: the most vertices (4 bytes of LDS each),
+// the most edges of an instance of a batch and of a graph traversed alone, and
+// threads.  One CU against a launch per round, in us, alone:
+//                        SSSP         BFS        CC
+//   R-MAT     2^14 edges  57 / 129    42 / 80    30 / 106
+//   R-MAT     2^16        87 / 136    59 / 81    58 / 106
+//   R-MAT     2^17       156 / 141    84 / 96    96 / 106
+//   uniform   2^14        60 / 125    37 / 59    30 / 92
+//   uniform   2^16       135 / 175    61 / 60    58 / 95
+//   uniform   2^17       227 / 199    81 / 62    94 / 97
+//   32 x 32 grid         107 / 331    94 / 133   25 / 127
+constexpr int kSmallN = 32768;
+constexpr long long kSmallM = 131072;
+inline long long small_max_edges(int algo) { return algo == 1 ? 32768 : 65536; }
+constexpr int kSmallBlock = 1024;
+// Bytes of LDS: 4 per vertex, 2 bits of frontier, and SSSP and BFS 4 per chunk
+// of a long row (rows of more than 64 edges in chunks of 256).
+inline size_t small_lds(int algo, int n, long long m) {
+    if (algo == 2) return sizeof(int) * (size_t)n;
+    return sizeof(int) * ((size_t)n + 2 * (((size_t)n + 31) / 32) + (size_t)(m / 65 + m / 256 + 1));
+}
+
 enum Kind { KIND_ROUND = 0, KIND_HEAVY = 1, KIND_AUX = 2 };
 
 enum Algo { SSSP = 0, BFS = 1, CC = 2 };
@@ -148,6 +170,8 @@ struct Round {
                     // CC: the both-directions rows) instead of pushing or sweeping
     int direct_lists; // SSSP local expansion: list passes issue their atomics without a
                       // check load of the head value
+    const int* inst; // batch of whole traversals: first vertex of each instance and the
+                     // end of the last, [nsrc + 1] (null otherwise)
     int item_shift; // log2 of the tiles of a frontier work item
     int* rmin;      // CC on a renumbered graph: per-label minimum of the caller's ids,
                     // filled with INT_MAX by the init kernel (null otherwise)
@@ -170,6 +194,11 @@ hipError_t launch_sssp_diropt(const Round& R, int grid, int block, hipStream_t s
 // link the rest; and the compression pass after a linking phase
 hipError_t launch_uf(const Round& R, int grid, int block, hipStream_t s);
 hipError_t launch_uf_compress(const Round& R, int grid, int block, hipStream_t s);
+// A whole traversal of a graph of at most kSmallN vertices (or, with R.inst,
+// those of a batch, the largest of max_n vertices and max_m edges) in one launch; a batch
+// clears the control block first
+hipError_t launch_small(const Round& R, int algo, int max_n, long long max_m, hipStream_t s);
+hipError_t launch_small_begin(const Round& R, hipStream_t s);
 // One thread stores v into the pinned host word *p (system scope) once every
 // earlier kernel of the stream has completed.
 hipError_t launch_mark(unsigned long long* p, unsigned long long v, hipStream_t s);

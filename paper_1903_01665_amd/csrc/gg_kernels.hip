@@ -28,6 +28,8 @@
 // than the heavy threshold are cut into fixed chunks and placed on a queue
 // that a second kernel of the same round spreads over the whole grid.
 
+#include <algorithm>
+
 #include "gg_internal.h"
 
 namespace gg {
@@ -1800,6 +1802,351 @@ GG_ROUND_KERNEL(8) void k_cc_diropt(Round R) {
     block_finish(R, acc, R.r % 3, KIND_ROUND);
 }
 
+// ----------------------------------------------- whole traversals in LDS ----
+// A graph of at most kSmallN vertices fits one workgroup: the values and two
+// generations of a frontier bitmap live in its LDS, the edges stream from the
+// L2, and the rounds are separated by workgroup barriers.  The whole traversal
+// is then one launch.  A round of
+// launches costs ~8 us on a graph this small, plus the empty rounds past the
+// end; here it costs what one CU needs for its edges (kSmallM in gg_internal.h
+// says up to which size that wins).  With R.inst every workgroup takes instances of
+// a batch, vertices [inst[i], inst[i+1]) with heads inside that range.
+
+constexpr int kSmallWaves = kSmallBlock / 64;
+
+struct SmallShared {
+    int queued;  // chunks of long rows of a round
+    int pushed;  // vertices it pushed (with repeats)
+};
+
+// Relax U edges per lane (t < 0: none), candidates cand: a head that drops goes
+// on the next frontier.  The drop is decided from the loaded value, so nothing
+// waits for an atomic (BFS: every lane of a round stores the same level).
+template <int A, int U>
+__device__ __forceinline__ void small_relax(int* dist, unsigned* nxt, const int (&t)[U],
+                                            const unsigned (&cand)[U], Acc& acc) {
+    unsigned cur[U];
+#pragma unroll
+    for (int j = 0; j < U; ++j) cur[j] = t[j] >= 0 ? (unsigned)dist[t[j]] : 0u;
+#pragma unroll
+    for (int j = 0; j < U; ++j) {
+        acc.e += t[j] >= 0;
+        if (cand[j] >= cur[j]) continue;
+        if (A == BFS) dist[t[j]] = (int)cand[j];
+        else atomicMin(&dist[t[j]], (int)cand[j]);
+        atomicOr(&nxt[t[j] >> 5], 1u << (t[j] & 31));
+        acc.p++;
+    }
+}
+
+// The np vertices listed in pend (one per lane).  Rows longer than
+// kSmallHeavy edges are queued in chunks for the whole workgroup; the others
+// take 16 lanes each, four rows per step with the loads of kSmallRows steps in
+// flight (a workgroup has 16 wavefronts to hide the L2's latency with, and a
+// uniform graph's rows of ~8 edges need no second step).
+constexpr int kSmallRows = 8;
+constexpr int kSmallHeavy = 64;
+constexpr int kSmallChunk = 256;
+constexpr int kSmallDense = 16;
+
+template <int A>
+__device__ __forceinline__ void small_serve(const Round& R, int base, int* dist, unsigned* nxt,
+                                            unsigned* queue, int* queued, const int* pend, int np,
+                                            int lev, Acc& acc) {
+    const DevGraph& g = R.g;
+    const int lane = threadIdx.x & 63;
+    __builtin_amdgcn_wave_barrier();
+    const int u = lane < np ? pend[lane] : -1;
+    __builtin_amdgcn_wave_barrier();
+    int rb = 0, deg = 0, sv = 0;
+    if (u >= 0) {
+        sv = A == BFS ? lev : dist[u];
+        rb = g.row[base + u];
+        deg = g.row[base + u + 1] - rb;
+        acc.v++;
+        if (deg > kSmallHeavy) {
+            const int c = (deg + kSmallChunk - 1) / kSmallChunk;
+            const int at = atomicAdd(queued, c);
+            for (int k = 0; k < c; ++k) queue[at + k] = (unsigned)u | (unsigned)k << 15;
+            deg = 0;
+        }
+    }
+    const int sub = lane & 15, grp = lane >> 4;
+    for (int s = 0; s * 4 < np; s += kSmallRows) {
+        int b[kSmallRows], d[kSmallRows], v[kSmallRows], more = 0;
+#pragma unroll
+        for (int j = 0; j < kSmallRows; ++j) {
+            const int o = (s + j) * 4 + grp;  // below 64: kSmallRows divides 16
+            b[j] = __shfl(rb, o, 64);
+            d[j] = __shfl(deg, o, 64);
+            v[j] = __shfl(sv, o, 64);
+            more = max(more, d[j]);
+        }
+        for (int k = sub; __ballot(k < more); k += 16) {
+            int t[kSmallRows];
+            unsigned c[kSmallRows];
+#pragma unroll
+            for (int j = 0; j < kSmallRows; ++j) {
+                t[j] = k < d[j] ? g.col[b[j] + k] - base : -1;
+                c[j] = A == SSSP && k < d[j] ? (unsigned)g.w[b[j] + k] : 1u;
+            }
+#pragma unroll
+            for (int j = 0; j < kSmallRows; ++j) c[j] += (unsigned)v[j];
+            small_relax<A>(dist, nxt, t, c, acc);
+        }
+    }
+}
+
+// One queued chunk of a long row, by one wavefront.
+template <int A>
+__device__ __forceinline__ void small_chunk(const Round& R, int base, int* dist, unsigned* nxt,
+                                            unsigned entry, int lev, Acc& acc) {
+    constexpr int U = kSmallChunk / 64;
+    const DevGraph& g = R.g;
+    const int u = (int)(entry & 32767u), lane = threadIdx.x & 63;
+    const int e0 = g.row[base + u] + (int)(entry >> 15) * kSmallChunk;
+    const int e1 = min(e0 + kSmallChunk, g.row[base + u + 1]);
+    const int sv = A == BFS ? lev : dist[u];
+    int t[U];
+    unsigned c[U];
+#pragma unroll
+    for (int j = 0; j < U; ++j) {
+        const int e = e0 + j * 64 + lane;
+        t[j] = e < e1 ? g.col[e] - base : -1;
+        c[j] = A == SSSP && e < e1 ? (unsigned)g.w[e] : 1u;
+    }
+#pragma unroll
+    for (int j = 0; j < U; ++j) c[j] += (unsigned)sv;
+    small_relax<A>(dist, nxt, t, c, acc);
+}
+
+// A dense round: every edge of the instance whose tail is reached (SSSP) or on
+// the level (BFS) is relaxed, four edges per 16-byte load, with no search for
+// rows and every lane busy; the next step's edges load while this one's are
+// relaxed.
+struct SmallEdges {
+    int u[4], t[4];
+    unsigned w[4];
+};
+
+template <int A>
+__device__ __forceinline__ SmallEdges small_edges(const DevGraph& g, int e, int e_begin,
+                                                  int e_end) {
+    SmallEdges x;
+    if (e >= e_begin && e + 4 <= e_end) {
+        const v4i a = *reinterpret_cast<const v4i*>(g.src + e);
+        const v4i b = *reinterpret_cast<const v4i*>(g.col + e);
+        v4i w = {1, 1, 1, 1};
+        if (A == SSSP) w = *reinterpret_cast<const v4i*>(g.w + e);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            x.u[i] = a[i];
+            x.t[i] = b[i];
+            x.w[i] = (unsigned)w[i];
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const bool in = e + i >= e_begin && e + i < e_end;
+            x.u[i] = in ? g.src[e + i] : -1;
+            x.t[i] = in ? g.col[e + i] : -1;
+            x.w[i] = A == SSSP && in ? (unsigned)g.w[e + i] : 1u;
+        }
+    }
+    return x;
+}
+
+template <int A>
+__device__ __forceinline__ void small_sweep(const Round& R, int base, int e_begin, int e_end,
+                                            int* dist, unsigned* nxt, int lev, Acc& acc) {
+    constexpr int step = kSmallBlock * 4;
+    int e = (e_begin & ~3) + (int)threadIdx.x * 4;
+    SmallEdges x = small_edges<A>(R.g, min(e, e_end), e_begin, e_end);
+    for (; e < e_end; e += step) {
+        const SmallEdges y = small_edges<A>(R.g, min(e + step, e_end), e_begin, e_end);
+        int t[4];
+        unsigned c[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int du = x.u[j] >= 0 ? dist[x.u[j] - base] : kInf;
+            const bool on = A == BFS ? du == lev : du != kInf;
+            t[j] = on ? x.t[j] - base : -1;
+            c[j] = (unsigned)du + x.w[j];
+        }
+        small_relax<A>(dist, nxt, t, c, acc);
+        x = y;
+    }
+}
+
+// One block's counters into its statistics slot (the only slots a whole
+// traversal writes), and the end of the traversal.
+__device__ void small_finish(const Round& R, const Acc& acc, int rounds) {
+    __shared__ int s_sum[kSmallWaves][4];
+    const int e = wave_sum(acc.e), v = wave_sum(acc.v), u = wave_sum(acc.u), p = wave_sum(acc.p);
+    if ((threadIdx.x & 63) == 0) {
+        int* s = s_sum[threadIdx.x >> 6];
+        s[0] = e;
+        s[1] = v;
+        s[2] = u;
+        s[3] = p;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        Stat st{0, 0, 0, 0, 0};
+        for (int i = 0; i < kSmallWaves; ++i) {
+            st.edges += s_sum[i][0];
+            st.verts += s_sum[i][1];
+            st.updates += s_sum[i][2];
+            st.pushes += s_sum[i][3];
+        }
+        R.ws.stat[KIND_ROUND * kMaxStatBlocks + blockIdx.x] = st;
+        // blocks of a batch: the most rounds (the control block was cleared)
+        if (R.inst) atomicMax(&R.ws.ctl->iters, rounds);
+        else R.ws.ctl->iters = rounds;
+        R.ws.ctl->done = 1;
+        __hip_atomic_store(R.host_done, R.epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
+}
+
+// SSSP and BFS: sparse rounds serve the frontier, dense ones sweep.  (SSSP's
+// near-far order gains nothing here: with a bucket of two mean weights 4096
+// vertices of a grid took 519 us, without 337; R-MAT and uniform graphs are
+// the same within 3%.)
+template <int A>
+__global__ __launch_bounds__(kSmallBlock) void k_small(Round R) {
+    extern __shared__ int s_mem[];
+    __shared__ int s_pend[kSmallWaves][64];
+    __shared__ SmallShared s_round[3];
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    const DevGraph& g = R.g;
+    int* pend = s_pend[wid];
+    Acc acc;
+    int rounds = 0;
+    const int count = R.inst ? R.nsrc : 1;
+    for (int i = blockIdx.x; i < count; i += gridDim.x) {
+        const int base = R.inst ? R.inst[i] : 0;
+        const int n = R.inst ? R.inst[i + 1] - base : R.g.n;
+        const int source = R.inst ? R.sources[i] - base : R.source;
+        const int words = (n + 31) / 32;
+        int* dist = s_mem;
+        unsigned* fb = reinterpret_cast<unsigned*>(s_mem + n);
+        const int e_begin = g.row[base], e_end = g.row[base + n];
+        unsigned* queue = fb + 2 * words;  // small_queue(most edges of an instance) entries
+        for (int v = threadIdx.x; v < n; v += kSmallBlock) dist[v] = v == source ? 0 : kInf;
+        for (int k = threadIdx.x; k < 2 * words; k += kSmallBlock)
+            fb[k] = k == (source >> 5) ? 1u << (source & 31) : 0;
+        if (threadIdx.x < 3) s_round[threadIdx.x] = SmallShared{0, 0};
+        __syncthreads();
+        int r = 0;
+        for (;; ++r) {
+            unsigned* cur = fb + (r & 1) * words;
+            unsigned* nxt = fb + ((r & 1) ^ 1) * words;
+            // slot r+1 = r-2 mod 3 was last read before round r-1's last barrier
+            if (threadIdx.x == 0) s_round[(r + 1) % 3] = SmallShared{0, 0};
+            SmallShared& sh = s_round[r % 3];
+            int np = 0;
+            // dense while the round before pushed more than n / kSmallDense
+            const int before = acc.p;
+            const bool dense = r > 0 && s_round[(r + 2) % 3].pushed > n / kSmallDense;
+            if (dense) {
+                for (int k = threadIdx.x; k < words; k += kSmallBlock) cur[k] = 0;
+                small_sweep<A>(R, base, e_begin, e_end, dist, nxt, r, acc);
+            } else {
+                // word k of the bitmap goes to wavefront k % kSmallWaves
+                for (int k0 = wid; k0 < words; k0 += kSmallBlock) {
+                    const int k = k0 + lane * kSmallWaves;
+                    unsigned word = k < words ? cur[k] : 0;
+                    if (word) cur[k] = 0;
+                    while (__ballot(word != 0)) {
+                        const bool on = word != 0;
+                        const int v = k * 32 + (on ? __ffs(word) - 1 : 0);
+                        word &= word - 1;
+                        const unsigned long long om = __ballot(on);
+                        const int c = __popcll(om);
+                        if (np + c > 64) {
+                            small_serve<A>(R, base, dist, nxt, queue, &sh.queued, pend, np, r, acc);
+                            np = 0;
+                        }
+                        if (on) pend[np + __popcll(om & ((1ull << lane) - 1))] = v;
+                        np += c;
+                    }
+                }
+                if (np > 0) small_serve<A>(R, base, dist, nxt, queue, &sh.queued, pend, np, r, acc);
+            }
+            __syncthreads();
+            const int nq = sh.queued;
+            for (int k = wid; k < nq; k += kSmallWaves)
+                small_chunk<A>(R, base, dist, nxt, queue[k], r, acc);
+            const int pushed = wave_sum(acc.p - before);
+            if (pushed && lane == 0) atomicAdd(&sh.pushed, pushed);
+            __syncthreads();
+            if (sh.pushed == 0) break;
+        }
+        rounds = max(rounds, r + 1);
+        for (int v = threadIdx.x; v < n; v += kSmallBlock) R.val[base + v] = dist[v];
+        __syncthreads();
+    }
+    small_finish(R, acc, rounds);
+}
+
+// CC through the union-find Set in LDS: every stored edge links its ends, the
+// larger root under the smaller, then every vertex takes its root.
+__global__ __launch_bounds__(kSmallBlock) void k_small_cc(Round R) {
+    extern __shared__ int s_mem[];
+    const DevGraph& g = R.g;
+    int* parent = s_mem;
+    for (int v = threadIdx.x; v < g.n; v += kSmallBlock) parent[v] = v;
+    __syncthreads();
+    Acc acc;
+    auto find = [&](int x) {
+        int p = parent[x];
+        while (p != x) {
+            const int gp = parent[p];
+            if (gp != p) parent[x] = gp;  // path halving: only non-roots change
+            x = gp;
+            p = parent[x];
+        }
+        return x;
+    };
+    for (int e0 = threadIdx.x; e0 < g.m; e0 += kSmallBlock * kBatch) {
+        int u[kBatch], v[kBatch];
+#pragma unroll
+        for (int j = 0; j < kBatch; ++j) {
+            const int e = e0 + j * kSmallBlock;
+            u[j] = e < g.m ? g.src[e] : 0;
+            v[j] = e < g.m ? g.col[e] : 0;
+        }
+#pragma unroll
+        for (int j = 0; j < kBatch; ++j) {
+            int a = u[j], b = v[j];
+            acc.e++;
+            for (;;) {
+                a = find(a);
+                b = find(b);
+                if (a == b) break;
+                const int hi = max(a, b), lo = min(a, b);
+                if (atomicCAS(&parent[hi], hi, lo) == hi) {
+                    acc.u++;
+                    break;
+                }
+            }
+        }
+    }
+    __syncthreads();
+    for (int v = threadIdx.x; v < g.n; v += kSmallBlock) {
+        int x = parent[v];
+        while (parent[x] != x) x = parent[x];
+        R.val[v] = x;
+        if (R.rmin) R.rmin[v] = kInf;
+    }
+    small_finish(R, acc, 1);
+}
+
+// The control block of a batch of whole traversals.
+__global__ __launch_bounds__(64) void k_small_begin(Round R) {
+    if (threadIdx.x == 0) *R.ws.ctl = Ctl{};
+}
+
 // ------------------------------------------------------- graph build ----
 
 // Edge-list sources: src[e] = the row u with row[u] <= e < row[u+1].  A
@@ -2396,6 +2743,36 @@ hipError_t launch_uf_compress(const Round& R, int grid, int block, hipStream_t s
 
 hipError_t launch_mark(unsigned long long* p, unsigned long long v, hipStream_t s) {
     hipLaunchKernelGGL(k_mark, dim3(1), dim3(64), 0, s, p, v);
+    return hipGetLastError();
+}
+
+// One workgroup for a single traversal, one per instance (at most a statistics
+// slot each) of a batch; LDS for the largest graph among them.
+hipError_t launch_small(const Round& R, int algo, int max_n, long long max_m, hipStream_t s) {
+    const void* f = algo == CC     ? reinterpret_cast<const void*>(k_small_cc)
+                    : algo == SSSP ? reinterpret_cast<const void*>(k_small<SSSP>)
+                                   : reinterpret_cast<const void*>(k_small<BFS>);
+    const size_t lds = small_lds(algo, max_n, max_m);
+    static const hipError_t allowed = [] {
+        const int most = (int)std::max(small_lds(SSSP, kSmallN, kSmallM), small_lds(CC, kSmallN, 0));
+        for (const void* k : {reinterpret_cast<const void*>(k_small_cc),
+                              reinterpret_cast<const void*>(k_small<SSSP>),
+                              reinterpret_cast<const void*>(k_small<BFS>)}) {
+            const hipError_t e =
+                hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, most);
+            if (e != hipSuccess) return e;
+        }
+        return hipSuccess;
+    }();
+    if (allowed != hipSuccess) return allowed;
+    const int grid = R.inst ? (R.nsrc < kMaxStatBlocks ? R.nsrc : kMaxStatBlocks) : 1;
+    Round arg = R;
+    void* args[] = {&arg};
+    return hipLaunchKernel(f, dim3(grid), dim3(kSmallBlock), args, lds, s);
+}
+
+hipError_t launch_small_begin(const Round& R, hipStream_t s) {
+    hipLaunchKernelGGL(k_small_begin, dim3(1), dim3(64), 0, s, R);
     return hipGetLastError();
 }
 

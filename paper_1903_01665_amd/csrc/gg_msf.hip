@@ -382,6 +382,7 @@ int gg_msf(gg_graph g, gg_ws ws, uint8_t* in_msf_dev, int64_t* total_weight, int
     ws->last_stream = s;
     ws->used = true;
     ws->profiled = false;
+    ws->small_blocks = 0;
     ws->last = gg_stats{};
     ws->last.algo = GG_ALGO_MSF;
     ws->last.status = status;

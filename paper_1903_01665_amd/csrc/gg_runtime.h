@@ -91,6 +91,7 @@ struct gg_ws_s {
     int nlaunch = 0;
     bool profiled = false;
     int rounds = 0;
+    int small_blocks = 0;  // blocks of the last whole traversal (0: it ran in rounds)
 };
 
 // The 64-bit batch sequence word inside a workspace's pinned block.
@@ -134,6 +135,11 @@ struct gg_graph_s {
     double avg_w = 0;  // mean edge weight (0 when unweighted)
     int max_w = 0;     // largest edge weight
     gg_ws_s* ws0 = nullptr;
+    // group of a batch whose instances all fit a workgroup: their vertex
+    // ranges (device, instances + 1) and the largest sizes among them
+    int* inst = nullptr;
+    int inst_max_n = 0;
+    long long inst_max_m = 0;
 };
 
 namespace gg {
@@ -178,6 +184,8 @@ struct Plan {
     Round R{};
     bool async = false, edge = false, cc = false, diropt = false, uf = false;
     bool need_heavy = false, need_jump = false, prof = false;
+    // the whole traversal is one launch (round 0; there is no init kernel)
+    bool whole = false;
     // renumbered graph: R.val is the workspace's array; the finishing
     // kernels write `out` in the caller's order
     bool renum = false;
