@@ -394,7 +394,7 @@ int gg_bfs_noalloc(gg_graph g, int32_t source, const gg_opts* opts, int32_t* dis
  * forest's edges and 0 for the others.  total_weight, n_edges (host,
  * nullable): the forest's summed weight and edge count.  ws NULL = the
  * graph's default workspace (the first call on a workspace allocates 12
- * bytes per vertex for the union-find, kept until the workspace is freed).
+ * bytes per vertex for the union-find and a bit per edge, kept until the workspace is freed).
  * GG_EINVAL for an unweighted graph or a NULL output with m > 0.  Returns
  * when the forest is complete. */
 int gg_msf(gg_graph g, gg_ws ws, uint8_t* in_msf_dev, int64_t* total_weight, int64_t* n_edges,

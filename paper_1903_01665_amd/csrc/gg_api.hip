@@ -62,6 +62,7 @@ void free_ws_arrays(gg_ws_s* ws) {
     if (ws->msf_best) (void)hipFree(ws->msf_best);
     ws->msf_parent = nullptr;
     ws->msf_best = nullptr;
+    dfree(ws->msf_mask);
     dfree(ws->rval);
     dfree(ws->rmin);
     for (auto& e : ws->ev)

@@ -12,7 +12,9 @@
 //   min      every edge whose ends lie in different components offers its key
 //            to both components (64-bit atomic minimum, checked first with a
 //            plain load); a component is named by its union-find root, and
-//            between rounds every vertex points at its root
+//            between rounds every vertex points at its root.  Offers to the
+//            roots a block meets first collect in its LDS and leave it as one
+//            atomic each
 //   link     every component with an offer joins the forest with its least
 //            edge (cut property) and merges with the other end's component
 //            in a lock-free union-find: the larger root is linked under the
@@ -23,10 +25,22 @@
 //            writes only its own vertex (a halving store of the first pass
 //            can land after the owner's own store, leaving an ancestor that
 //            is not the root; the offers of the next round need the root)
-// A round with no crossing edge ends the run; the next round's first kernel
+// The rounds come in two phases.  The first takes only the light edges, those
+// up to a sampled quantile of the weights (about kLightPerVertex edges per
+// vertex): the least crossing light edge of a component is its least crossing
+// edge, so every choice stands, and most of the graph is one component before
+// the bulk of the edges is looked at.  The second phase takes every edge.  The
+// first round of a phase scans all edges and leaves a bit per edge that still
+// crosses; the later rounds read only those.  A round with no crossing edge
+// ends its phase, the second phase the run; the next round's first kernel
 // reports it (same protocol as the traversal rounds).  Each round at least
 // halves the number of components that still have a crossing edge, so
-// log2(n) + 2 rounds suffice.
+// 2 log2(n) + 4 rounds suffice.
+//
+// Atomics bound the offers: 27 G/s at most on this device, 2-8 G/s on skewed
+// addresses, against 60-400 G/s for loads.  With every edge offered in every
+// round an R-MAT graph of 2^20 vertices and 2^24 edges took 1.35, 2.22, 0.20
+// and 0.07 ms of offers, the whole forest 4.1 ms; now 0.8 ms.
 
 #include <new>
 
@@ -37,8 +51,20 @@ using namespace gg;
 namespace {
 
 constexpr unsigned long long kNoEdge = ~0ull;
-constexpr int kMsfMaxRounds = 40;
-constexpr int kMsfBatch = 4;
+constexpr int kMsfMaxRounds = 72;
+// A work item is 1 or 4 steps of 256 edges, four per lane: one step while
+// that leaves no more than an item for each of kFillWaves wavefronts (a 256 x
+// 256 grid's forest: 398 us with four steps, 312 with one).
+constexpr int kMsfSteps = 4;
+constexpr int kMsfSlots = 1024;  // roots whose offers a block collects
+// Light edges per vertex, and the most of the edges that may be light: below
+// five edges per vertex one phase is faster (a uniform graph of 2^17 vertices
+// and 2^19 edges 0.60 ms in two phases, 0.53 in one; of 2^21 and 2^24 2.15 and
+// 2.67; R-MAT, sixteen per vertex, the same within 8% from 0.5 to 3 per vertex).
+constexpr double kLightPerVertex = 1.0;
+constexpr double kLightMost = 0.2;
+constexpr int kMsfSample = 8192;  // weights sampled for the light quantile
+constexpr int kMsfBatch = 2;
 
 struct Msf {
     const int* src;
@@ -47,6 +73,10 @@ struct Msf {
     const int* eorig;          // renumbered graph: caller's index of each stored edge
     const int* epos;           // ... and stored place of each caller edge (else null)
     int n, m;
+    int max_w;                 // largest weight
+    int steps;                 // 256-edge steps of a work item
+    int light;                 // samples (of kMsfSample) up to the light weight; 0: one phase
+    unsigned long long* mask;  // a bit per edge: crossing when its phase last looked
     int* parent;               // union-find forest
     unsigned long long* best;  // per root: least key of a crossing edge
     unsigned char* in_msf;     // [m] output
@@ -63,30 +93,37 @@ __device__ __forceinline__ int wsum(int x) {
     return x;
 }
 
-// Per-block plain update of a statistics slot (edges, updates) and of the
-// round's flag.
-__device__ void msf_finish(const Msf& M, int kind, int edges, int crossing, int links) {
+// Per-block plain update of a statistics slot (edges, updates, the weight of
+// the forest's edges in `swept`) and of the round's flag.
+__device__ void msf_finish(const Msf& M, int kind, int edges, int crossing, int links,
+                           long long weight) {
     __shared__ int s_v[3][4];
+    __shared__ long long s_w[4];
     const int a = wsum(edges), b = wsum(crossing), c = wsum(links);
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) weight += __shfl_xor(weight, d, 64);
     const int wid = threadIdx.x >> 6;
     if ((threadIdx.x & 63) == 0) {
         s_v[0][wid] = a;
         s_v[1][wid] = b;
         s_v[2][wid] = c;
+        s_w[wid] = weight;
     }
     __syncthreads();
     if (threadIdx.x == 0) {
-        long long E = 0, X = 0, L = 0;
+        long long E = 0, X = 0, L = 0, W = 0;
         for (int i = 0; i < (int)(blockDim.x >> 6); ++i) {
             E += s_v[0][i];
             X += s_v[1][i];
             L += s_v[2][i];
+            W += s_w[i];
         }
         if (E | X | L) {
             Stat* st = M.stat + kind * kMaxStatBlocks + blockIdx.x;
             st->edges += E;
             st->verts += X;
             st->updates += L;
+            st->swept += W;
         }
         if (X > 0) M.ctl->changed[M.r % 3] = 1;
     }
@@ -104,54 +141,168 @@ __global__ __launch_bounds__(256) void k_msf_init(Msf M) {
     if (tid == 0) *M.ctl = Ctl{};
 }
 
+// The light weight: the least x with at least M.light of kMsfSample weights,
+// spread over the edges by a multiplicative hash, up to x.
+__global__ __launch_bounds__(1024) void k_msf_light(Msf M) {
+    constexpr int P = kMsfSample / 1024;
+    __shared__ int s_c[16];
+    int x[P];
+#pragma unroll
+    for (int i = 0; i < P; ++i) {
+        const unsigned h = (unsigned)(i * 1024 + (int)threadIdx.x) * 2654435761u;
+        x[i] = M.w[(int)((unsigned long long)h * (unsigned)M.m >> 32)];
+    }
+    int lo = 0, hi = M.max_w;  // the answer lies in [lo, hi]
+    while (lo < hi) {
+        const int mid = lo + (hi - lo) / 2;
+        int c = 0;
+#pragma unroll
+        for (int i = 0; i < P; ++i) c += x[i] <= mid;
+        c = wsum(c);
+        if ((threadIdx.x & 63) == 0) s_c[threadIdx.x >> 6] = c;
+        __syncthreads();
+        c = 0;
+        for (int i = 0; i < 16; ++i) c += s_c[i];
+        __syncthreads();
+        if (c >= M.light) hi = mid;
+        else lo = mid + 1;
+    }
+    if (threadIdx.x == 0) M.ctl->bound[3] = lo;
+}
+
 // Round entry: false once the run has ended (the kernel that sees round r-1
-// without a crossing edge records the round count and tells the host).
-__device__ __forceinline__ bool msf_begin(const Msf& M) {
+// without a crossing edge in the last phase records the round count and tells
+// the host).  Every block derives the phase from round r-1's slots.
+__device__ __forceinline__ bool msf_begin(const Msf& M, bool& light, bool& first) {
     Ctl* ctl = M.ctl;
     if (*(volatile int*)&ctl->done) return false;
-    if (M.r > 0 && *(volatile int*)&ctl->changed[(M.r - 1) % 3] == 0) {
-        if (blockIdx.x == 0 && threadIdx.x == 0) {
-            ctl->iters = M.r;
-            ctl->done = 1;
-            __hip_atomic_store(M.host_done, M.tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    light = M.light > 0;
+    first = M.r == 0;
+    if (M.r > 0) {
+        const bool was = *(volatile int*)&ctl->pull[(M.r - 1) % 3] != 0;
+        light = was;
+        if (*(volatile int*)&ctl->changed[(M.r - 1) % 3] == 0) {
+            if (!was) {
+                if (blockIdx.x == 0 && threadIdx.x == 0) {
+                    ctl->iters = M.r;
+                    ctl->done = 1;
+                    __hip_atomic_store(M.host_done, M.tag, __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_SYSTEM);
+                }
+                return false;
+            }
+            light = false;
+            first = true;
         }
-        return false;
     }
-    if (blockIdx.x == 0 && threadIdx.x == 0) ctl->changed[(M.r + 1) % 3] = 0;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        ctl->changed[(M.r + 1) % 3] = 0;
+        ctl->pull[M.r % 3] = light;
+    }
     return true;
 }
 
-__device__ __forceinline__ bool offer(const Msf& M, int u, int v, int e) {
-    if (u == v) return false;
+struct Offers {
+    int* tag;                 // [kMsfSlots] root of each slot, -1 free
+    unsigned long long* key;  // its least offer in this block
+};
+
+__device__ __forceinline__ void offer_to(const Msf& M, const Offers& o, int root,
+                                         unsigned long long key) {
+    const int h = (int)((unsigned)root * 2654435761u >> 22);  // kMsfSlots = 2^10
+    int tag = o.tag[h];
+    if (tag < 0) {
+        tag = atomicCAS(&o.tag[h], -1, root);
+        if (tag < 0) tag = root;
+    }
+    if (tag == root) {
+        if (key < o.key[h])
+            __hip_atomic_fetch_min(&o.key[h], key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    } else if (key < M.best[root]) {
+        atomicMin(&M.best[root], key);
+    }
+}
+
+__device__ __forceinline__ bool offer(const Msf& M, const Offers& o, int u, int v, int w, int e) {
     const int ru = M.parent[u], rv = M.parent[v];
     if (ru == rv) return false;
     const int eo = M.eorig ? M.eorig[e] : e;
-    const unsigned long long key = ((unsigned long long)(unsigned)M.w[e] << 32) | (unsigned)eo;
-    if (key < M.best[ru]) atomicMin(&M.best[ru], key);
-    if (key < M.best[rv]) atomicMin(&M.best[rv], key);
+    const unsigned long long key = ((unsigned long long)(unsigned)w << 32) | (unsigned)eo;
+    offer_to(M, o, ru, key);
+    offer_to(M, o, rv, key);
     return true;
 }
 
-__global__ __launch_bounds__(256) void k_msf_min(Msf M) {
-    if (!msf_begin(M)) return;
-    const long long tid = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    const long long tt = (long long)gridDim.x * blockDim.x;
+// A wavefront takes M.steps * 256 consecutive edges, four per lane at a time;
+// bit `lane` of mask word 4 * (256-edge step) + j stands for a lane's j-th edge.
+__global__ __launch_bounds__(256, 7) void k_msf_min(Msf M) {
+    bool light, first;
+    if (!msf_begin(M, light, first)) return;
+    __shared__ int s_tag[kMsfSlots];
+    __shared__ unsigned long long s_key[kMsfSlots];
+    for (int i = threadIdx.x; i < kMsfSlots; i += blockDim.x) {
+        s_tag[i] = -1;
+        s_key[i] = kNoEdge;
+    }
+    __syncthreads();
+    const Offers o{s_tag, s_key};
+    const int lane = threadIdx.x & 63;
+    const int wpb = blockDim.x >> 6;
+    const long long gw = (long long)blockIdx.x * wpb + (threadIdx.x >> 6);
+    const long long tw = (long long)gridDim.x * wpb;
+    const int words = 4 * M.steps;
+    const long long items = ((long long)M.m + 256 * M.steps - 1) / (256 * M.steps);
+    const int top = light ? M.ctl->bound[3] : 2147483647;
     int edges = 0, crossing = 0;
-    const long long m4 = M.m & ~3LL;
-    for (long long e = tid * 4; e < m4; e += tt * 4) {
-        const int4 s4 = *reinterpret_cast<const int4*>(M.src + e);
-        const int4 c4 = *reinterpret_cast<const int4*>(M.col + e);
-        edges += 4;
-        crossing += offer(M, s4.x, c4.x, (int)e);
-        crossing += offer(M, s4.y, c4.y, (int)e + 1);
-        crossing += offer(M, s4.z, c4.z, (int)e + 2);
-        crossing += offer(M, s4.w, c4.w, (int)e + 3);
+    for (long long it = gw; it < items; it += tw) {
+        unsigned long long* mask = M.mask + it * words;
+        unsigned long long word = ~0ull;
+        if (!first) {
+            word = lane < words ? mask[lane] : 0;
+            if (__ballot(word != 0) == 0) continue;
+        }
+        unsigned long long left = 0;  // lane 4c + j keeps word 4c + j
+        for (int c = 0; c < M.steps; ++c) {
+            const long long e = (it * M.steps + c) * 256 + lane * 4;
+            unsigned todo = 0;
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                todo |= (unsigned)((__shfl(word, 4 * c + j, 64) >> lane) & 1) << j;
+            int u[4] = {0, 0, 0, 0}, v[4] = {0, 0, 0, 0}, w[4] = {0, 0, 0, 0};
+            if (todo && e + 4 <= M.m) {
+                const int4 w4 = *reinterpret_cast<const int4*>(M.w + e);
+                const int4 s4 = *reinterpret_cast<const int4*>(M.src + e);
+                const int4 c4 = *reinterpret_cast<const int4*>(M.col + e);
+                u[0] = s4.x, u[1] = s4.y, u[2] = s4.z, u[3] = s4.w;
+                v[0] = c4.x, v[1] = c4.y, v[2] = c4.z, v[3] = c4.w;
+                w[0] = w4.x, w[1] = w4.y, w[2] = w4.z, w[3] = w4.w;
+            } else if (todo) {
+                for (int j = 0; j < 4; ++j)
+                    if (e + j < M.m) {
+                        u[j] = M.src[e + j];
+                        v[j] = M.col[e + j];
+                        w[j] = M.w[e + j];
+                    }
+            }
+            // edges past the end have equal ends
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const bool on = ((todo >> j) & 1) && u[j] != v[j] && w[j] <= top;
+                edges += on;
+                const bool x = on && offer(M, o, u[j], v[j], w[j], (int)(e + j));
+                crossing += x;
+                const unsigned long long b = __ballot(x);
+                if (lane == 4 * c + j) left = b;
+            }
+        }
+        if (lane < words && (first || left != word)) mask[lane] = left;
     }
-    for (long long e = m4 + tid; e < M.m; e += tt) {
-        edges++;
-        crossing += offer(M, M.src[e], M.col[e], (int)e);
+    __syncthreads();
+    for (int i = threadIdx.x; i < kMsfSlots; i += blockDim.x) {
+        const int root = s_tag[i];
+        if (root >= 0 && s_key[i] < M.best[root]) atomicMin(&M.best[root], s_key[i]);
     }
-    msf_finish(M, KIND_ROUND, edges, crossing, 0);
+    msf_finish(M, KIND_ROUND, edges, crossing, 0, 0);
 }
 
 // Union-find accesses while links happen: device-scope atomics, so every
@@ -178,6 +329,7 @@ __global__ __launch_bounds__(256) void k_msf_link(Msf M) {
     const long long tid = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     const long long tt = (long long)gridDim.x * blockDim.x;
     int links = 0;
+    long long weight = 0;
     for (long long v = tid; v < M.n; v += tt) {
         const unsigned long long b = M.best[v];
         if (b == kNoEdge) continue;
@@ -199,12 +351,15 @@ __global__ __launch_bounds__(256) void k_msf_link(Msf M) {
             int expect = a;
             if (__hip_atomic_compare_exchange_strong(M.parent + a, &expect, c, __ATOMIC_RELAXED,
                                                      __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
+                // every edge of the forest links once: two components that
+                // chose the same edge are one after the first link
                 ++links;
+                weight += (long long)(b >> 32);
                 break;
             }
         }
     }
-    msf_finish(M, KIND_AUX, 0, 0, links);
+    msf_finish(M, KIND_AUX, 0, 0, links, weight);
 }
 
 __global__ __launch_bounds__(256) void k_msf_compress(Msf M) {
@@ -237,18 +392,13 @@ __global__ __launch_bounds__(256) void k_msf_settle(Msf M) {
     }
 }
 
-// Weight and edge count of the forest: one pair of 64-bit partial sums per
-// block.
-__global__ __launch_bounds__(256) void k_msf_sum(const unsigned char* in_msf, const int* w,
-                                                 const int* epos, int m, long long* partial) {
-    const long long tid = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    const long long tt = (long long)gridDim.x * blockDim.x;
+// Weight and edge count of the forest from the links' statistics slots.
+__global__ __launch_bounds__(256) void k_msf_sum(const Stat* stat, long long* sum) {
     long long sw = 0, cnt = 0;
-    for (long long e = tid; e < m; e += tt)
-        if (in_msf[e]) {
-            sw += w[epos ? epos[e] : e];
-            cnt++;
-        }
+    for (int i = threadIdx.x; i < kMaxStatBlocks; i += 256) {
+        sw += stat[KIND_AUX * kMaxStatBlocks + i].swept;
+        cnt += stat[KIND_AUX * kMaxStatBlocks + i].updates;
+    }
     __shared__ long long s_w[4], s_c[4];
     for (int d = 32; d > 0; d >>= 1) {
         sw += __shfl_xor(sw, d, 64);
@@ -260,13 +410,8 @@ __global__ __launch_bounds__(256) void k_msf_sum(const unsigned char* in_msf, co
     }
     __syncthreads();
     if (threadIdx.x == 0) {
-        long long a = 0, b = 0;
-        for (int i = 0; i < (int)(blockDim.x >> 6); ++i) {
-            a += s_w[i];
-            b += s_c[i];
-        }
-        partial[2 * blockIdx.x] = a;
-        partial[2 * blockIdx.x + 1] = b;
+        sum[0] = s_w[0] + s_w[1] + s_w[2] + s_w[3];
+        sum[1] = s_c[0] + s_c[1] + s_c[2] + s_c[3];
     }
 }
 
@@ -308,6 +453,9 @@ int gg_msf(gg_graph g, gg_ws ws, uint8_t* in_msf_dev, int64_t* total_weight, int
         HIPCHK(g, hipMalloc(&p, sizeof(unsigned long long) * (size_t)n));
         ws->msf_best = static_cast<unsigned long long*>(p);
     }
+    const int steps = (m + 255LL) / 256 <= kFillWaves ? 1 : kMsfSteps;
+    const long long items = ((long long)m + 256 * steps - 1) / (256 * steps);
+    if (!ws->msf_mask) HIPCHK(g, dalloc(&ws->msf_mask, (size_t)items * 4 * steps));
     if (ws->used && ws->last_stream != s) HIPCHK(g, hipStreamWaitEvent(s, ws->finished, 0));
     hipError_t e = hipSuccess;
     const int tag = reserve_stamps(ws, s, kMsfMaxRounds + 2, &e);
@@ -320,6 +468,11 @@ int gg_msf(gg_graph g, gg_ws ws, uint8_t* in_msf_dev, int64_t* total_weight, int
     M.epos = g->renumbered ? g->epos : nullptr;
     M.n = n;
     M.m = m;
+    const double share = m > 0 ? kLightPerVertex * n / m : 1.0;
+    M.steps = steps;
+    M.light = share < kLightMost ? std::max(1, (int)(share * kMsfSample)) : 0;
+    M.max_w = g->max_w;
+    M.mask = ws->msf_mask;
     M.parent = ws->msf_parent;
     M.best = ws->msf_best;
     M.in_msf = in_msf_dev;
@@ -328,10 +481,14 @@ int gg_msf(gg_graph g, gg_ws ws, uint8_t* in_msf_dev, int64_t* total_weight, int
     M.host_done = ws->h_done;
     M.tag = tag;
     const int g_init = msf_grid(reinterpret_cast<const void*>(k_msf_init), std::max(n, m));
-    const int g_min = msf_grid(reinterpret_cast<const void*>(k_msf_min), (m + 3) / 4);
+    const int g_min = msf_grid(reinterpret_cast<const void*>(k_msf_min), items * 64);
     const int g_vert = msf_grid(reinterpret_cast<const void*>(k_msf_link), n);
     hipLaunchKernelGGL(k_msf_init, dim3(g_init), dim3(kBlock), 0, s, M);
     HIPCHK(g, hipGetLastError());
+    if (M.light > 0) {
+        hipLaunchKernelGGL(k_msf_light, dim3(1), dim3(1024), 0, s, M);
+        HIPCHK(g, hipGetLastError());
+    }
     // batches of rounds, two outstanding, as in the traversal driver
     int r = 0, k = 0, status = GG_OK;
     auto enqueue = [&]() -> hipError_t {
@@ -361,23 +518,15 @@ int gg_msf(gg_graph g, gg_ws ws, uint8_t* in_msf_dev, int64_t* total_weight, int
         HIPCHK(g, enqueue());
     }
     // forest weight and size
-    long long* partial = reinterpret_cast<long long*>(ws->dev.pcount);
-    const int g_sum = msf_grid(reinterpret_cast<const void*>(k_msf_sum), m);
-    std::vector<long long> hp(2 * (size_t)g_sum);
-    hipLaunchKernelGGL(k_msf_sum, dim3(g_sum), dim3(kBlock), 0, s, in_msf_dev, g->w, M.epos, m,
-                       partial);
+    long long* sum = reinterpret_cast<long long*>(ws->dev.pcount);
+    long long hs[2] = {0, 0};
+    hipLaunchKernelGGL(k_msf_sum, dim3(1), dim3(kBlock), 0, s, ws->dev.stat, sum);
     HIPCHK(g, hipGetLastError());
-    HIPCHK(g, hipMemcpyAsync(hp.data(), partial, sizeof(long long) * hp.size(),
-                             hipMemcpyDeviceToHost, s));
+    HIPCHK(g, hipMemcpyAsync(hs, sum, sizeof(hs), hipMemcpyDeviceToHost, s));
     HIPCHK(g, hipEventRecord(ws->finished, s));
     HIPCHK(g, hipEventSynchronize(ws->finished));
-    long long tw = 0, cnt = 0;
-    for (int i = 0; i < g_sum; ++i) {
-        tw += hp[2 * (size_t)i];
-        cnt += hp[2 * (size_t)i + 1];
-    }
-    if (total_weight) *total_weight = tw;
-    if (n_edges) *n_edges = cnt;
+    if (total_weight) *total_weight = hs[0];
+    if (n_edges) *n_edges = hs[1];
     ws->rounds = r;
     ws->last_stream = s;
     ws->used = true;

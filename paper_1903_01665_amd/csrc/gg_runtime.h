@@ -71,10 +71,11 @@ struct gg_ws_s {
     // completed, written by a marker kernel (non-blocking driving)
     int* h_done = nullptr;
     unsigned long long prog_seq = 0;  // last sequence number enqueued
-    // minimum spanning forest: union-find parents and per-root offers,
-    // allocated by the first gg_msf call on the workspace
+    // minimum spanning forest: union-find parents, per-root offers and crossing
+    // edges, allocated by the first gg_msf call on the workspace
     int* msf_parent = nullptr;
     unsigned long long* msf_best = nullptr;
+    unsigned long long* msf_mask = nullptr;  // a bit per edge
     // renumbered graph: the traversal's values in the library's vertex order
     // and the per-component minimum of the caller's ids (CC)
     int* rval = nullptr;
