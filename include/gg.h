@@ -102,13 +102,14 @@ typedef enum { GG_VERTEX = 0, GG_EDGE = 1, GG_MODE_AUTO = 2 } gg_mode;
  * for CC, vertex otherwise).
  * GG_UNIONFIND (CC only, vertex-based; needs the both-directions CSR): the
  *   components through the DSL's Set type, a union-find structure (Sec. 2):
- *   every vertex is linked with its first and then its second neighbour
- *   (each pass followed by a compression), the root most of 1024 sampled
- *   vertices share is taken as the giant component's, and only the vertices
- *   outside it link their remaining neighbours (Sutton, Ben-Nun and Barak's
- *   Afforest).  Linking hangs the larger root under the smaller, so the
- *   labels are the same: the smallest id of each component.  Four rounds,
- *   whatever the graph's diameter. */
+ *   every vertex hangs under the smallest of its first neighbours, the roots
+ *   left hook under smaller neighbouring trees (each pass followed by a
+ *   compression), the root most of 1024 sampled vertices share is taken as
+ *   the giant component's, and only the vertices outside it link all their
+ *   neighbours (the order of Sutton, Ben-Nun and Barak's Afforest).  The
+ *   larger root always hangs under the smaller, so the labels are the same:
+ *   the smallest id of each component.  Four rounds, whatever the graph's
+ *   diameter. */
 typedef enum {
     GG_SYNC = 0,
     GG_ASYNC = 1,

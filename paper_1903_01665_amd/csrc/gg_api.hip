@@ -686,9 +686,23 @@ hipError_t plan_round(Plan& p, int r) {
         e = plan_launch(p, KIND_HEAVY, [&] { return launch_heavy(R, p.algo, p.g_heavy, kBlock, p.s); });
     if (e == hipSuccess && p.need_jump)
         e = plan_launch(p, KIND_AUX, [&] { return launch_jump(R, p.g_jump, kBlock, p.s); });
-    // union-find: a compression after each linking phase
-    if (e == hipSuccess && p.uf && r != 2 && r <= 3)
-        e = plan_launch(p, KIND_AUX, [&] { return launch_uf_compress(R, p.g_round, kBlock, p.s); });
+    // union-find: the chains of a deep graph, the hooking passes of round 1,
+    // and a compression after each step but the sampling
+    auto compress = [&](int pass) {
+        return plan_launch(p, KIND_AUX,
+                           [&] { return launch_uf_compress(R, pass, p.g_round, kBlock, p.s); });
+    };
+    if (p.uf && r == 0 && p.g->levels >= 256)
+        for (int k = 0; k < kUfDoubles && e == hipSuccess; ++k)
+            e = plan_launch(p, KIND_AUX,
+                            [&] { return launch_uf_double(R, p.g_round, kBlock, p.s); });
+    const UfPlan uf = uf_plan(p.g->n, p.g->ms);
+    for (int k = 0; p.uf && r == 1 && k < uf.passes && e == hipSuccess; ++k) {
+        e = plan_launch(p, KIND_AUX,
+                        [&] { return launch_uf_hook(R, k, uf.share, p.g_round, kBlock, p.s); });
+        if (e == hipSuccess) e = compress(k);
+    }
+    if (e == hipSuccess && p.uf && (r == 0 || r == 3)) e = compress(-1);
     return e;
 }
 

@@ -22,6 +22,21 @@ constexpr int kChunk = 512;          // most edges per heavy-row chunk
 constexpr int kKinds = 3;            // statistics kinds: round, heavy chunks, auxiliary
 constexpr int kItemTiles = 8;        // most tiles of a frontier work item
 constexpr int kFillWaves = 8192;     // wavefronts that fill the device (256 CUs x 32)
+// Hooking passes of CC by union-find and, for all but the first, the share of
+// the vertices they look from: by the neighbours a vertex has (ms / n, both
+// directions).  Trees of a sparse graph touch in few places: with 2 neighbours
+// a vertex (2^18 vertices) three passes leave enough apart that linking the
+// rest takes 1.30 ms, with five passes all of CC takes 0.13; with 4 neighbours
+// (2^22 vertices) three take 0.75, five 1.15 ms; with 8 three passes from one
+// vertex in eight do (2^20 vertices: 0.19 ms).
+struct UfPlan {
+    int passes, share;
+};
+inline UfPlan uf_plan(long long n, long long ms) {
+    if (ms >= 8 * n) return UfPlan{3, 8};
+    return UfPlan{ms >= 3 * n ? 3 : 5, 1};
+}
+constexpr int kUfDoubles = 3;        // its passes over the chains of a deep graph
 constexpr int kXcd = 8;              // accelerator dies; workgroups go to them round-robin
 // Tiles per frontier work item, as a shift: the most (up to kItemTiles) that
 // still leave an item for each of kFillWaves wavefronts.  Graphs of 4M
@@ -88,7 +103,7 @@ struct Ctl {
     int hgrid[4];    // [r % 3] = grid of round r's heavy kernel
     int pull[4];     // [r % 3] = round r took the dense form (BFS pull, CC edge sweep)
     int giant;       // CC by union-find: the root most sampled vertices have
-    int pad[1];
+    int hooked[8];   // ... and whether its hooking pass [k] hooked anything
 };
 
 // Per-block counters, summed on the host after a traversal; one array of
@@ -190,10 +205,15 @@ hipError_t launch_bfs_diropt(const Round& R, int grid, int block, hipStream_t s)
 hipError_t launch_jump(const Round& R, int grid, int block, hipStream_t s);
 hipError_t launch_cc_diropt(const Round& R, int grid, int block, hipStream_t s);
 hipError_t launch_sssp_diropt(const Round& R, int grid, int block, hipStream_t s);
-// CC by union-find (GG_UNIONFIND), phase R.r: link, find the giant root,
-// link the rest; and the compression pass after a linking phase
+// CC by union-find (GG_UNIONFIND), round R.r: join, nothing, find the giant
+// root, link the rest; the hooking passes of round 1; the kUfDoubles
+// passes after round 0 on a deep graph; and the compression after each
 hipError_t launch_uf(const Round& R, int grid, int block, hipStream_t s);
-hipError_t launch_uf_compress(const Round& R, int grid, int block, hipStream_t s);
+hipError_t launch_uf_hook(const Round& R, int pass, int share, int grid, int block,
+                          hipStream_t s);
+hipError_t launch_uf_double(const Round& R, int grid, int block, hipStream_t s);
+// pass: the hooking pass before it (-1: none)
+hipError_t launch_uf_compress(const Round& R, int pass, int grid, int block, hipStream_t s);
 // A whole traversal of a graph of at most kSmallN vertices (or, with R.inst,
 // those of a batch, the largest of max_n vertices and max_m edges) in one launch; a batch
 // clears the control block first

@@ -2373,19 +2373,34 @@ __global__ __launch_bounds__(256) void k_t_fill(const int* col, const int* w, co
 
 // ----------------------------------------------------- CC by union-find ----
 // The DSL's Set type is a union-find structure (Sec. 2); CC over it, in the
-// order of Sutton, Ben-Nun and Barak's Afforest: every vertex is linked with
-// its first neighbour (phase 0) and its second (phase 1) in the
-// both-directions rows, each followed by a compression; phase 2 samples the
-// roots of 1024 vertices and takes the most frequent as the giant
-// component's; phase 3 links, for every vertex outside that component, all
-// its remaining neighbours (an edge with one end in the giant component is
-// seen from the other end; edges inside it need nothing), and a last
-// compression makes every parent a root.  Linking hangs the larger of two
-// roots under the smaller with a compare-and-swap, so a root is always the
-// smallest id of its tree, and the parent array ends as the smallest id of
-// each component -- the labels of the other schedules.  The value array is
-// the parent array (labels start as the ids).  Phases set the round's
-// change flag except the last, so the round after it ends the traversal.
+// order of Sutton, Ben-Nun and Barak's Afforest: join every vertex with a few
+// neighbours, find the giant component by sampling, link the rest outside it.
+// Round 0 links nothing: every vertex takes the smallest of itself and its
+// first kUfFirst neighbours (both-directions rows) as its parent, a plain
+// store of a smaller id, so the parents are a forest whose roots are the
+// vertices without a smaller neighbour among those.  Round 1 hooks the roots
+// under smaller neighbouring trees, by plain stores too (k_uf_hook).  Round 2
+// samples the roots of 1024 vertices and takes the most frequent as the giant
+// component's; round 3 links, for every vertex outside that component, all its
+// neighbours (an edge with one end in the giant component is seen from the
+// other end; edges inside it need nothing), hanging the larger of two roots
+// under the smaller with a compare-and-swap.  Every step but the sampling is
+// followed by a compression with path halving (every vertex walks, so a long
+// chain is halved by all of its vertices at once), the last by one in which
+// every vertex writes only its own root.  A parent is always a smaller id of
+// the same component, so a root is the smallest id of its tree, and the parent
+// array ends as the smallest id of each component -- the labels of the other
+// schedules.  The value array is the parent array (labels start as the ids).
+// Rounds set the change flag except the last, so the round after it ends the
+// traversal.
+//
+// Bound by dependent gathers of parents.  Linking every vertex with its first
+// two neighbours by compare-and-swap built deep trees under contention: 7.4 ms
+// on a uniform graph of 2^23 vertices and 2^26 edges, where edge sweeps take
+// 2.5 ms; linking only round 0's roots 2.4 ms; now 0.93 ms (R-MAT, 2^22
+// vertices and 2^26 edges: 0.30 -> 0.23 ms).
+constexpr int kUfFirst = 8;
+
 __device__ __forceinline__ int uf_load(int* p, int x) {
     return __hip_atomic_load(p + x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
@@ -2426,52 +2441,59 @@ __global__ __launch_bounds__(256) void k_uf(Round R) {
     const long long tid = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     const long long tt = (long long)gridDim.x * blockDim.x;
     Acc acc;
-    if (R.r <= 1) {
+    if (R.r == 0) {
         for (long long v = tid; v < g.n; v += tt) {
-            const int b = g.srow[v];
-            if (g.srow[v + 1] - b > R.r) {
-                acc.e++;
-                acc.u += uf_link(parent, (int)v, g.scol[b + R.r]);
+            const int b = g.srow[v], e1 = min(b + kUfFirst, g.srow[v + 1]);
+            int x[kUfFirst], least = (int)v;
+#pragma unroll
+            for (int k = 0; k < kUfFirst; ++k) x[k] = b + k < e1 ? g.scol[b + k] : (int)v;
+#pragma unroll
+            for (int k = 0; k < kUfFirst; ++k) least = min(least, x[k]);
+            acc.e += e1 - b;
+            if (least < v) {
+                parent[v] = least;
+                acc.u++;
             }
         }
     } else if (R.r == 2) {
         // the giant component's root: the most frequent root of 1024
-        // vertices spread over the ids (a multiplicative hash of i)
-        __shared__ int s_root[1024];
+        // vertices spread over the ids (a multiplicative hash of i), counted
+        // in an open-addressing table
+        constexpr int kSlots = 2048;
+        __shared__ int s_root[kSlots], s_count[kSlots];
+        __shared__ unsigned long long s_best;
         if (blockIdx.x == 0) {
+            for (int i = threadIdx.x; i < kSlots; i += blockDim.x) {
+                s_root[i] = -1;
+                s_count[i] = 0;
+            }
+            if (threadIdx.x == 0) s_best = 0;
+            __syncthreads();
             for (int i = threadIdx.x; i < 1024; i += blockDim.x) {
                 const unsigned h = (unsigned)i * 2654435761u;
-                s_root[i] = parent[(int)((unsigned long long)h * (unsigned)g.n >> 32)];
-            }
-            __syncthreads();
-            int best = -1, best_count = 0;
-            for (int i = threadIdx.x; i < 1024; i += blockDim.x) {
-                int c = 0;
-                for (int k = 0; k < 1024; ++k) c += s_root[k] == s_root[i];
-                if (c > best_count || (c == best_count && s_root[i] < best)) {
-                    best_count = c;
-                    best = s_root[i];
+                const int x = parent[(int)((unsigned long long)h * (unsigned)g.n >> 32)];
+                int k = (int)((unsigned)x * 2654435761u >> 21);
+                for (;; k = (k + 1) & (kSlots - 1)) {
+                    const int was = atomicCAS(&s_root[k], -1, x);
+                    if (was == -1 || was == x) break;
                 }
+                atomicAdd(&s_count[k], 1);
             }
-            __shared__ int s_bc[256], s_b[256];
-            s_bc[threadIdx.x] = best_count;
-            s_b[threadIdx.x] = best;
             __syncthreads();
-            if (threadIdx.x == 0) {
-                for (int i = 1; i < (int)blockDim.x; ++i)
-                    if (s_bc[i] > best_count || (s_bc[i] == best_count && s_b[i] < best)) {
-                        best_count = s_bc[i];
-                        best = s_b[i];
-                    }
-                R.ws.ctl->giant = best;
-            }
+            // the most frequent, the smallest id among equals
+            for (int i = threadIdx.x; i < kSlots; i += blockDim.x)
+                if (s_count[i] > 0)
+                    atomicMax(&s_best, (unsigned long long)s_count[i] << 32 |
+                                           (unsigned)(kInf - s_root[i]));
+            __syncthreads();
+            if (threadIdx.x == 0) R.ws.ctl->giant = kInf - (int)(s_best & 0xffffffffu);
         }
     } else if (R.r == 3) {
         const int giant = *(volatile int*)&R.ws.ctl->giant;
         for (long long v = tid; v < g.n; v += tt) {
-            if (parent[v] == giant) continue;  // roots after the compression
+            if (parent[v] == giant) continue;
             const int b = g.srow[v], e1 = g.srow[v + 1];
-            for (int e = b + 2; e < e1; ++e) {
+            for (int e = b; e < e1; ++e) {
                 acc.e++;
                 acc.u += uf_link(parent, (int)v, g.scol[e]);
             }
@@ -2484,16 +2506,90 @@ __global__ __launch_bounds__(256) void k_uf(Round R) {
     block_finish(R, acc, R.r % 3, KIND_ROUND);
 }
 
-// Every parent to its root; each thread writes its own vertex only.
-__global__ __launch_bounds__(256) void k_uf_compress(Round R) {
+// Round 1, pass `pass`.  Pass 0: every root takes the smallest parent that its
+// first neighbours have.  The roots it leaves have mostly neighbours of their
+// own tree, so the later passes look from one vertex in `share` (another
+// each pass), which hooks its parent, a root after the compression.  Several
+// vertices may hook one root; the last store stands, and a join that is lost
+// so is found again in round 3 unless both its trees are in the giant one.
+// After a pass from the vertices that hooked nothing the rest return at once.
+template <bool ROOTS>
+__global__ __launch_bounds__(256) void k_uf_hook(Round R, int pass, int share, int first) {
+    Ctl* ctl = R.ws.ctl;
+    if (*(volatile int*)&ctl->done || (pass > 1 && !*(volatile int*)&ctl->hooked[pass - 1])) return;
+    const DevGraph& g = R.g;
+    bool hooked = false;
+    int* parent = R.val;
+    constexpr int K = ROOTS ? kUfFirst : kUfFirst / 2;
+    const long long step = ROOTS ? 1 : share;
+    const long long tid = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    const long long tt = (long long)gridDim.x * blockDim.x;
+    for (long long v = tid * step + first; v < g.n; v += tt * step) {
+        const int r = parent[v];
+        if (ROOTS && r != v) continue;
+        const int b = g.srow[v], e1 = min(b + K, g.srow[v + 1]);
+        int x[K], least = r;
+#pragma unroll
+        for (int k = 0; k < K; ++k) x[k] = b + k < e1 ? g.scol[b + k] : (int)v;
+#pragma unroll
+        for (int k = 0; k < K; ++k) x[k] = parent[x[k]];
+#pragma unroll
+        for (int k = 0; k < K; ++k) least = min(least, x[k]);
+        if (least < r) {
+            parent[r] = least;
+            hooked = true;
+        }
+    }
+    if (__syncthreads_or(hooked) && threadIdx.x == 0) ctl->hooked[pass] = 1;
+}
+
+// Every vertex two parents higher.  On a deep graph round 0 leaves chains as
+// long as the graph is deep (a 4096 x 4096 grid: a chain per column), which
+// the walks of the compression below climb slowly: all of CC 2.06 ms, with
+// kUfDoubles of these passes first 0.78 ms.
+__global__ __launch_bounds__(256) void k_uf_double(Round R) {
     if (*(volatile int*)&R.ws.ctl->done) return;
     int* parent = R.val;
     const long long tid = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     const long long tt = (long long)gridDim.x * blockDim.x;
     for (long long v = tid; v < R.g.n; v += tt) {
-        int x = parent[v];
-        while (parent[x] != x) x = parent[x];
-        parent[v] = x;
+        const int p = parent[v], x = parent[p], y = parent[x];
+        if (y != p) parent[v] = y;
+    }
+}
+
+// Every parent to its root.  LAST: each thread writes its own vertex only (a
+// halving store can land after the owner's own and leave an ancestor that is
+// not the root).
+template <bool LAST>
+__global__ __launch_bounds__(256) void k_uf_compress(Round R, int pass) {
+    if (*(volatile int*)&R.ws.ctl->done || (pass >= 0 && !*(volatile int*)&R.ws.ctl->hooked[pass]))
+        return;
+    int* parent = R.val;
+    const long long tid = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    const long long tt = (long long)gridDim.x * blockDim.x;
+    for (long long v = tid; v < R.g.n; v += tt) {
+        const int p = parent[v];
+        int x = parent[p], y = p;
+        if (x == p) continue;
+        if (LAST) {
+            while (x != y) {
+                y = x;
+                x = parent[x];
+            }
+            parent[v] = x;
+        } else {
+            // y's parent x differs from y: hang v, then every vertex met,
+            // two steps higher
+            int at = (int)v;
+            while (x != y) {
+                parent[at] = x;
+                at = x;
+                y = parent[at];
+                x = parent[y];
+            }
+            parent[v] = y;
+        }
     }
 }
 
@@ -2737,8 +2833,19 @@ hipError_t launch_uf(const Round& R, int grid, int block, hipStream_t s) {
     GG_LAUNCH(k_uf, grid, block, s, R);
 }
 
-hipError_t launch_uf_compress(const Round& R, int grid, int block, hipStream_t s) {
-    GG_LAUNCH(k_uf_compress, grid, block, s, R);
+hipError_t launch_uf_hook(const Round& R, int pass, int share, int grid, int block,
+                          hipStream_t s) {
+    if (pass == 0) GG_LAUNCH(k_uf_hook<true>, grid, block, s, R, pass, 1, 0);
+    GG_LAUNCH(k_uf_hook<false>, grid, block, s, R, pass, share, (pass - 1) % share);
+}
+
+hipError_t launch_uf_double(const Round& R, int grid, int block, hipStream_t s) {
+    GG_LAUNCH(k_uf_double, grid, block, s, R);
+}
+
+hipError_t launch_uf_compress(const Round& R, int pass, int grid, int block, hipStream_t s) {
+    if (R.r == 3) GG_LAUNCH(k_uf_compress<true>, grid, block, s, R, pass);
+    GG_LAUNCH(k_uf_compress<false>, grid, block, s, R, pass);
 }
 
 hipError_t launch_mark(unsigned long long* p, unsigned long long v, hipStream_t s) {
