@@ -2,12 +2,10 @@
 //
 // A traversal is an init kernel followed by rounds (one kernel each, plus a
 // heavy-chunk kernel or a CC shortcut kernel where the variant needs one).
-// The host enqueues rounds in batches that double in size up to kMaxBatch;
-// after each batch it copies the device `done` flag into pinned memory and
-// records an event.  While batch k runs, the host waits for batch k-1's event
-// and stops enqueueing once that batch reported `done`.  Rounds enqueued past
-// the end return at their first instruction, so the overshoot costs at most
-// one batch of empty launches.
+// The host keeps a few rounds enqueued beyond the one the device is in
+// (round kernels tell it through pinned memory) and stops once a round kernel
+// reports the end; the rounds enqueued past it return at their first
+// instruction.
 
 #include <gg.h>
 
@@ -96,7 +94,7 @@ int make_ws(gg_graph g, gg_ws_s** out) {
     if (e == hipSuccess) e = dalloc(&ws->dev.pcount, (size_t)3 * 2 * kMaxStatBlocks);
     if (e == hipSuccess && g->renumbered) e = dalloc(&ws->rval, (size_t)g->n);
     if (e == hipSuccess && g->renumbered) e = dalloc(&ws->rmin, (size_t)g->n);
-    if (e == hipSuccess) e = hipHostMalloc(reinterpret_cast<void**>(&ws->h_done), 4 * sizeof(int));
+    if (e == hipSuccess) e = hipHostMalloc(reinterpret_cast<void**>(&ws->h_done), 6 * sizeof(int));
     if (e == hipSuccess) e = hipEventCreateWithFlags(&ws->ev[0], hipEventDisableTiming);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&ws->ev[1], hipEventDisableTiming);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&ws->finished, hipEventDisableTiming);
@@ -119,6 +117,7 @@ int make_ws(gg_graph g, gg_ws_s** out) {
     ws->dev.tflag[1] = ws->vflag_mem + 2 * vbytes + tbytes;
     ws->h_done[0] = -1;
     *prog_word(ws) = 0;
+    *round_word(ws) = ~0ull;  // no traversal's tag
     *out = ws;
     return GG_OK;
 }
@@ -554,6 +553,7 @@ int plan_make(gg_graph g, gg_ws ws, int algo, int source, const int* sources_dev
     R.mapping = o.mapping;
     R.jump = p.cc && !(o.flags & GG_OPT_CC_NO_JUMP);
     R.host_done = ws->h_done;
+    R.host_round = ws->h_done ? round_word(ws) : nullptr;
     // default bucket width: a few mean weights (one bucket then spans paths
     // of several light edges)
     R.delta = nearfar ? std::max(1, o.delta) : 0;
@@ -748,11 +748,6 @@ int reserve_stamps(gg_ws ws, hipStream_t s, long long span, hipError_t* err) {
     return base;
 }
 
-// Eager driver as a resumable state machine.  Batches of rounds double in
-// size up to kMaxBatch; at most two batches are outstanding.  When the older
-// one has completed, the pinned word tells whether some round kernel found
-// the end (it stores the traversal's tag); if not, the next batch goes out.
-// Rounds enqueued past the end return at their first instruction.
 // Bound on the rounds of a traversal.  Every round of a sweep or worklist
 // schedule that changes something fixes at least one more vertex, so n + 2
 // rounds suffice; a near-far round may only raise the bound, which happens
@@ -765,128 +760,98 @@ long long max_rounds(const Plan& p) {
     return std::min(r, 1LL << 30);
 }
 
-int drive_start(Drive& d, long long r0, int stamp_base, int tag) {
-    d.r = r0;
-    d.batch = 2;
-    d.k = 0;
-    d.stamp_base = stamp_base;
-    d.tag = tag;
-    d.max_rounds = max_rounds(d.p);
-    d.t0 = std::chrono::steady_clock::now();
-    d.status = GG_OK;
-    d.finished = false;
-    d.stopping = false;
-    d.finishing = false;
-    d.fin_seq = 0;
-    // two batches in flight from the start (a whole traversal is one launch:
-    // its batch stands as the older of the two)
-    for (int i = 0; i < (d.p.whole ? 1 : 2); ++i) {
-        int rc = drive_enqueue(d);
-        if (rc != GG_OK) return rc;
+// Eager driver as a resumable state machine.  Every round kernel tells the host
+// that its round is running, and the host keeps a few rounds enqueued beyond it
+// (kAhead, kAheadPolled) until a round kernel reports the end by storing the
+// traversal's tag into the pinned word.  Rounds enqueued past the end return at
+// their first instruction.  A whole traversal is one launch, whose completion
+// is waited for: it reports from the kernel that writes the values.
+static int drive_mark(Drive& d) {
+    Plan& p = d.p;
+    if (d.poll) {
+        d.seq = ++p.ws->prog_seq;
+        HIPCHK(p.g, launch_mark(prog_word(p.ws), d.seq, p.s));
+    } else {
+        HIPCHK(p.g, hipEventRecord(p.ws->ev[0], p.s));
     }
-    if (d.p.whole) d.k = 2;
     return GG_OK;
 }
 
-int drive_enqueue(Drive& d) {
+// Whether what drive_mark marked has completed (1; 0: not yet, poll only).
+static int drive_marked(Drive& d) {
+    if (d.poll) return __atomic_load_n(prog_word(d.p.ws), __ATOMIC_ACQUIRE) >= d.seq;
+    HIPCHK(d.p.g, hipEventSynchronize(d.p.ws->ev[0]));
+    return 1;
+}
+
+static bool drive_reported(const Drive& d) {
+    return __atomic_load_n(d.p.ws->h_done, __ATOMIC_ACQUIRE) == d.tag;
+}
+
+// Rounds reached, as the device last told.
+static long long drive_reached(const Drive& d) {
+    const unsigned long long x = __atomic_load_n(round_word(d.p.ws), __ATOMIC_ACQUIRE);
+    return (unsigned)(x >> 32) == (unsigned)d.tag ? (long long)(unsigned)x : 0;
+}
+
+int drive_start(Drive& d, long long r0, int stamp_base, int tag) {
     Plan& p = d.p;
-    const long long stop = std::min(d.r + d.batch, d.max_rounds);
+    d.r = r0;
+    d.stamp_base = stamp_base;
+    d.tag = tag;
+    d.max_rounds = max_rounds(p);
+    d.t0 = std::chrono::steady_clock::now();
+    d.status = GG_OK;
+    d.finished = d.stopping = d.finishing = false;
+    const long long stop = std::min(r0 + (d.poll ? kAheadPolled : kAhead), d.max_rounds);
     for (; d.r < stop; ++d.r) HIPCHK(p.g, plan_round(p, (int)d.r));
-    if (d.poll) {
-        const unsigned long long v = ++p.ws->prog_seq;
-        HIPCHK(p.g, launch_mark(prog_word(p.ws), v, p.s));
-        d.seq[d.k & 1] = v;
-    } else {
-        HIPCHK(p.g, hipEventRecord(p.ws->ev[d.k & 1], p.s));
-    }
-    ++d.k;
-    d.batch = std::min(d.batch * 2, kMaxBatch);
-    return GG_OK;
+    return p.whole ? drive_mark(d) : GG_OK;
 }
 
 // The rounds are over (the end was reported, or rounds or time ran out).
 // Without finishing kernels the traversal is finished now; otherwise they
-// are enqueued once, followed by a marker (polled) or an event, and the
-// traversal is finished when that has run: its output is then complete.
-int drive_end(Drive& d, bool block) {
+// are enqueued once, and the traversal is finished when they have run: its
+// output is then complete.
+static int drive_end(Drive& d) {
     Plan& p = d.p;
-    gg_ws ws = p.ws;
-    if (!p.renum) {
-        d.finished = true;
-        return 1;
-    }
-    if (!d.finishing) {
-        HIPCHK(p.g, plan_finish(p));
-        d.finishing = true;
-        if (d.poll) {
-            d.fin_seq = ++ws->prog_seq;
-            HIPCHK(p.g, launch_mark(prog_word(ws), d.fin_seq, p.s));
-        } else {
-            // the older batch's event has completed: its slot is free
-            HIPCHK(p.g, hipEventRecord(ws->ev[d.k & 1], p.s));
+    if (p.renum) {
+        if (!d.finishing) {
+            HIPCHK(p.g, plan_finish(p));
+            d.finishing = true;
+            const int rc = drive_mark(d);
+            if (rc != GG_OK) return rc;
         }
-    }
-    if (d.poll) {
-        if (__atomic_load_n(prog_word(ws), __ATOMIC_ACQUIRE) < d.fin_seq) return 0;
-    } else if (block) {
-        HIPCHK(p.g, hipEventSynchronize(ws->ev[d.k & 1]));
-    } else {
-        const hipError_t q = hipEventQuery(ws->ev[d.k & 1]);
-        if (q == hipErrorNotReady) return 0;
-        HIPCHK(p.g, q);
+        const int rc = drive_marked(d);
+        if (rc <= 0) return rc;
     }
     d.finished = true;
     return 1;
 }
 
-int drive_step(Drive& d, bool block) {
+int drive_step(Drive& d) {
     if (d.finished) return 1;
-    if (d.finishing) return drive_end(d, block);
+    if (d.finishing) return drive_end(d);
     Plan& p = d.p;
-    gg_ws ws = p.ws;
-    auto reported = [&] { return __atomic_load_n(ws->h_done, __ATOMIC_ACQUIRE) == d.tag; };
-    auto completed = [&](int slot) { return __atomic_load_n(prog_word(ws), __ATOMIC_ACQUIRE) >= d.seq[slot]; };
-    // batch k-2 is the older of the two outstanding (k-1 the newer one)
-    if (d.poll) {
-        if (reported() && !p.whole) {
-            // the values are final once the end is found; rounds still queued
-            // return at their first instruction.  (A whole traversal reports
-            // from the kernel that writes the values: its batch's marker
-            // must have run.)
-            return drive_end(d, block);
-        }
-        if (d.stopping) {
-            // out of rounds or time: the newer batch must complete before the
-            // status is final (checked on later steps, never waited for here)
-            if (!completed((d.k + 1) & 1)) return 0;
-            if (!reported()) d.status = d.stop_status;
-            return drive_end(d, block);
-        }
-        if (!completed(d.k & 1)) return 0;
-    } else if (block) {
-        HIPCHK(p.g, hipEventSynchronize(ws->ev[d.k & 1]));
-    } else {
-        const hipError_t q = hipEventQuery(ws->ev[d.k & 1]);
-        if (q == hipErrorNotReady) return 0;
-        HIPCHK(p.g, q);
+    if (d.stopping || p.whole) {
+        const int rc = drive_marked(d);
+        if (rc <= 0) return rc;
+        if (!drive_reported(d)) d.status = p.whole ? GG_EHIP : d.stop_status;
+        return drive_end(d);
     }
-    if (reported()) return drive_end(d, block);
-    const long long ms = std::chrono::duration_cast<std::chrono::milliseconds>(
-                             std::chrono::steady_clock::now() - d.t0).count();
-    if (d.r >= d.max_rounds || ms > p.o.time_limit_ms) {
-        const int st = d.r >= d.max_rounds ? GG_EITER : GG_ETIMEOUT;
-        if (d.poll) {
-            d.stopping = true;
-            d.stop_status = st;
-            if (!completed((d.k + 1) & 1)) return 0;
-        } else {
-            HIPCHK(p.g, hipEventSynchronize(ws->ev[(d.k + 1) & 1]));
-        }
-        if (!reported()) d.status = st;
-        return drive_end(d, block);
+    // the values are final once the end is found
+    if (drive_reported(d)) return drive_end(d);
+    const long long stop =
+        std::min(drive_reached(d) + (d.poll ? kAheadPolled : kAhead), d.max_rounds);
+    const bool late = std::chrono::steady_clock::now() - d.t0 >
+                      std::chrono::milliseconds(p.o.time_limit_ms);
+    if (d.r >= d.max_rounds || late) {
+        // what is enqueued must complete before the status is final
+        d.stopping = true;
+        d.stop_status = d.r >= d.max_rounds ? GG_EITER : GG_ETIMEOUT;
+        return drive_mark(d);
     }
-    int rc = drive_enqueue(d);
-    return rc == GG_OK ? 0 : rc;
+    for (; d.r < stop; ++d.r) HIPCHK(p.g, plan_round(p, (int)d.r));
+    return 0;
 }
 
 // Blocking form: run the state machine to the end.
@@ -895,8 +860,9 @@ int plan_drive(Plan& p, long long r0, int stamp_base, int tag, long long* r_end)
     d.p = p;
     int rc = drive_start(d, r0, stamp_base, tag);
     while (rc == GG_OK) {
-        rc = drive_step(d, true);
+        rc = drive_step(d);
         if (rc == 1) break;
+        __builtin_ia32_pause();
     }
     *r_end = d.r;
     if (rc < 0) return rc;

@@ -114,7 +114,7 @@ void engine_loop(Engine* E) {
         for (size_t i = 0; i < mine.size();) {
             gg_ticket t = mine[i];
             const long long r0 = t->d.r;
-            const int rc = drive_step(t->d, false);
+            const int rc = drive_step(t->d);
             if (rc == 0) {
                 moved |= t->d.r != r0;
                 ++i;

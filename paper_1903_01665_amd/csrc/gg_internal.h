@@ -174,6 +174,7 @@ struct Round {
     int r;       // round (sweep, level) index
     int epoch;   // tag of this traversal: grows across the traversals of a workspace
     int* host_done; // pinned host word: set to `epoch` by the kernel that finds the end
+    unsigned long long* host_round; // pinned: epoch << 32 | rounds reached (null: not reported)
     int mapping; // Map
     int jump;    // CC: apply the label[label[v]] shortcut
     int delta;   // SSSP near-far schedule: bucket width (0 = plain worklist rounds)

@@ -220,6 +220,15 @@ __device__ void block_finish(const Round& R, const Acc& a, int slot, int kind, i
                 (int)(c < 2147483647LL ? c : 2147483647LL);
         }
         if (blockIdx.x == 0) {
+            // rounds reached, for the host (which enqueues a few rounds
+            // ahead).  Stored here and not when the round begins: the
+            // wavefront would wait for the store's way to host memory with
+            // its first loads (8 us of each round of a 1023 x 777 grid).
+            if (kind == KIND_ROUND && R.host_round)
+                __hip_atomic_store(
+                    R.host_round,
+                    (unsigned long long)(unsigned)R.epoch << 32 | (unsigned)(R.r + 1),
+                    __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
             if (pk == KIND_ROUND) R.ws.ctl->grid[slot] = gridDim.x;
             if (pk == KIND_HEAVY) R.ws.ctl->hgrid[slot] = gridDim.x;
         }

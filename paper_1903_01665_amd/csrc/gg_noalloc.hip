@@ -112,6 +112,7 @@ extern "C" int gg_bfs_noalloc(gg_graph g, int32_t source, const gg_opts* opts,
     p.prof = false;  // profiling would create events
     // the end word is in the array: read back with a copy, not polled
     p.R.host_done = done_word;
+    p.R.host_round = nullptr;
 
     // the call's tag (tags restart long before the int range ends)
     const long long span = (long long)g->n + 3;

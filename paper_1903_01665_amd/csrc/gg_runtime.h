@@ -20,7 +20,17 @@ namespace gg {
 constexpr int kVersion = 1;
 constexpr int kBlock = 256;
 constexpr int kHeavyPerWave = 4;  // heavy-row chunks a wavefront of the chunk kernel checks
-constexpr int kMaxBatch = 16;
+constexpr int kMaxBatch = 16;     // most rounds enqueued at once (allocation-free BFS)
+// Rounds the host keeps enqueued beyond the last one reported.  A round
+// past the end is a launch or two that return at once, but each takes the
+// device 2-5 us, and whatever follows the traversal waits for it.  Batches of
+// 2, 4, 8 and 16 rounds left up to 19 of them: BFS of a 3.0M-vertex R-MAT graph
+// 0.37 ms with batches, 0.29 with four rounds ahead; the plain worklist on one
+// of 2^18 vertices 0.54 and 0.48 ms.  A round of ~5 us needs about three ahead
+// of it to hide the host's launches.
+constexpr int kAhead = 4;
+// ... of each of the traversals a driver thread advances in turn
+constexpr int kAheadPolled = 8;
 constexpr int kDefaultTimeLimitMs = 60000;
 
 struct Dev {
@@ -68,7 +78,8 @@ struct gg_ws_s {
     int epoch = 0;  // round stamps of the next traversal start here
     // pinned host words: [0] the tag written by the kernel that finds the
     // end; [2..3] (64 bits) the sequence number of the last batch of rounds
-    // completed, written by a marker kernel (non-blocking driving)
+    // completed, written by a marker kernel (non-blocking driving); [4..5] the
+    // rounds reached, written by the round kernels
     int* h_done = nullptr;
     unsigned long long prog_seq = 0;  // last sequence number enqueued
     // minimum spanning forest: union-find parents, per-root offers and crossing
@@ -98,6 +109,11 @@ struct gg_ws_s {
 // The 64-bit batch sequence word inside a workspace's pinned block.
 inline unsigned long long* prog_word(gg_ws ws) {
     return reinterpret_cast<unsigned long long*>(ws->h_done + 2);
+}
+
+// The 64-bit word of the rounds reached inside a workspace's pinned block.
+inline unsigned long long* round_word(gg_ws ws) {
+    return reinterpret_cast<unsigned long long*>(ws->h_done + 4);
 }
 
 struct gg_graph_s {
@@ -210,35 +226,30 @@ int reserve_stamps(gg_ws ws, hipStream_t s, long long span, hipError_t* err);
 // Resumable eager driver of one traversal (see gg_api.hip).
 struct Drive {
     Plan p;
-    long long r = 0, max_rounds = 0;
-    int batch = 2, k = 0;
-    // poll: batches end with a marker kernel that stores their sequence
-    // number into pinned memory (read without any runtime call); otherwise
-    // with an event the host waits on
+    long long r = 0, max_rounds = 0;  // rounds enqueued, and the most there can be
+    // poll: advanced by a driver thread that never waits: ends are marked by a
+    // kernel that stores a sequence number into pinned memory (read without
+    // any runtime call); otherwise the calling thread waits
     bool poll = false;
-    unsigned long long seq[2] = {0, 0};
+    unsigned long long seq = 0;  // poll: sequence number of the marker enqueued last
     int stamp_base = 0, tag = 0;
     std::chrono::steady_clock::time_point t0;
     int status = GG_OK;
     bool finished = false;
-    // poll: out of rounds or time, waiting for the newer batch to complete
-    // before stop_status becomes final
+    // out of rounds or time: the enqueued rounds must complete before
+    // stop_status becomes final
     bool stopping = false;
     int stop_status = GG_OK;
-    // poll, renumbered graph: the finishing kernels are enqueued and the
-    // traversal ends when the marker after them has run
+    // renumbered graph: the finishing kernels are enqueued
     bool finishing = false;
-    unsigned long long fin_seq = 0;
 };
 // Bound on the rounds of a traversal planned by p.
 long long max_rounds(const Plan& p);
-// Enqueue the first two batches of rounds from round r0.
+// Enqueue the first rounds, from round r0.
 int drive_start(Drive& d, long long r0, int stamp_base, int tag);
-// Enqueue the next batch.
-int drive_enqueue(Drive& d);
 // Advance: 1 = finished (d.status holds GG_OK, GG_EITER or GG_ETIMEOUT),
 // 0 = still running (non-blocking form only), < 0 = HIP failure.
-int drive_step(Drive& d, bool block);
+int drive_step(Drive& d);
 // Blocking form: rounds from r0 until the end is reported.
 int plan_drive(Plan& p, long long r0, int stamp_base, int tag, long long* r_end);
 // Upload of a renumbered graph: order each row's edges by head (gg_sort.hip).

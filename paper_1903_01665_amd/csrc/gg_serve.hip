@@ -216,7 +216,7 @@ bool step_locked(gg_server s) {
     for (size_t i = 0; i < s->active.size();) {
         Query* q = s->active[i];
         const long long r_before = q->d.r;
-        const int rc = drive_step(q->d, false);
+        const int rc = drive_step(q->d);
         if (rc == 0) {
             moved |= q->d.r != r_before;
             ++i;
