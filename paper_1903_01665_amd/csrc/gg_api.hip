@@ -609,6 +609,7 @@ int plan_make(gg_graph g, gg_ws ws, int algo, int source, const int* sources_dev
     // ... and the shortcut kernel of a CC pull round
     if (diropt && p.cc && R.pullmode) p.need_jump = true;
     p.g_jump = grid((n + kBlock - 1) / kBlock);
+    R.front_bits = diropt && algo == GG_ALGO_BFS && !g->renumbered && n >= kFrontBitsN;
     return GG_OK;
 }
 
@@ -686,6 +687,13 @@ hipError_t plan_round(Plan& p, int r) {
         e = plan_launch(p, KIND_HEAVY, [&] { return launch_heavy(R, p.algo, p.g_heavy, kBlock, p.s); });
     if (e == hipSuccess && p.need_jump)
         e = plan_launch(p, KIND_AUX, [&] { return launch_jump(R, p.g_jump, kBlock, p.s); });
+    if (e == hipSuccess && R.front_bits) {
+        Round next = R;
+        next.r = r + 1;
+        const int words = (R.g.n + 31) / 32;
+        const int gb = std::max(1, std::min(p.g_round, (words + 4 * kBlock - 1) / (4 * kBlock)));
+        e = plan_launch(p, KIND_AUX, [&] { return launch_front_bits(next, gb, kBlock, p.s); });
+    }
     // union-find: the chains of a deep graph, the hooking passes of round 1,
     // and a compression after each step but the sampling
     auto compress = [&](int pass) {

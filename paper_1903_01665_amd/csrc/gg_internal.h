@@ -85,6 +85,16 @@ inline size_t small_lds(int algo, int n, long long m) {
     return sizeof(int) * ((size_t)n + 2 * (((size_t)n + 31) / 32) + (size_t)(m / 65 + m / 256 + 1));
 }
 
+// Vertices from which a pulled BFS round looks its in-neighbours up in a bitmap
+// of the frontier (a bit per vertex, resident in every die's L2) instead of in
+// the values, on graphs stored in the caller's order.  Values that outgrow the
+// L2 are gathered at 62-76 G/s, the bits at ~230; the launch that makes them
+// costs ~3 us a round whether it pulls or not.  Uniform graphs: 2^23 vertices and
+// 2^26 edges 1.17 -> 0.84 ms, 2^22 and 2^25 0.92 -> 0.58, 2^21 and 2^24 0.44 ->
+// 0.34 (values of 8 MB); a renumbered R-MAT graph gathers its hot values at
+// 200 G/s as they are.
+constexpr int kFrontBitsN = 1 << 21;
+
 enum Kind { KIND_ROUND = 0, KIND_HEAVY = 1, KIND_AUX = 2 };
 
 enum Algo { SSSP = 0, BFS = 1, CC = 2 };
@@ -188,6 +198,7 @@ struct Round {
                       // check load of the head value
     const int* inst; // batch of whole traversals: first vertex of each instance and the
                      // end of the last, [nsrc + 1] (null otherwise)
+    int front_bits; // direction-optimizing BFS: pulled rounds read the frontier as bits
     int item_shift; // log2 of the tiles of a frontier work item
     int* rmin;      // CC on a renumbered graph: per-label minimum of the caller's ids,
                     // filled with INT_MAX by the init kernel (null otherwise)
@@ -203,6 +214,8 @@ hipError_t launch_vasync(const Round& R, int algo, int grid, int block, hipStrea
 hipError_t launch_easync(const Round& R, int algo, int grid, int block, hipStream_t s);
 hipError_t launch_heavy(const Round& R, int algo, int grid, int block, hipStream_t s);
 hipError_t launch_bfs_diropt(const Round& R, int grid, int block, hipStream_t s);
+// ... and the bits of the frontier of round R.r, launched after round R.r - 1
+hipError_t launch_front_bits(const Round& R, int grid, int block, hipStream_t s);
 hipError_t launch_jump(const Round& R, int grid, int block, hipStream_t s);
 hipError_t launch_cc_diropt(const Round& R, int grid, int block, hipStream_t s);
 hipError_t launch_sssp_diropt(const Round& R, int grid, int block, hipStream_t s);

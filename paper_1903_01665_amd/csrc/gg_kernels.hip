@@ -1467,17 +1467,21 @@ GG_ROUND_KERNEL(8) void k_bfs_diropt(Round R) {
                 acc.v++;
             }
             const int* icol = g.symmetric ? g.col : g.scol;
+            const unsigned* fb = R.front_bits ? R.ws.hbits[cur] : nullptr;
+            auto on_level = [&](int u) {
+                return fb ? ((fb[u >> 5] >> (u & 31)) & 1u) != 0 : val[u] == lev;
+            };
             bool found = false;
             // short lists: each lane walks its own, kBatch entries at a time
             const bool shortl = todo && ie - ib <= 64;
             for (int e = ib; shortl && !found && e < ie; e += kBatch) {
-                int x[kBatch];
+                bool x[kBatch];
 #pragma unroll
-                for (int j = 0; j < kBatch; ++j) x[j] = e + j < ie ? val[icol[e + j]] : kInf;
+                for (int j = 0; j < kBatch; ++j) x[j] = e + j < ie && on_level(icol[e + j]);
 #pragma unroll
                 for (int j = 0; j < kBatch; ++j) {
                     if (e + j < ie) acc.e++;
-                    found |= x[j] == lev;
+                    found |= x[j];
                 }
             }
             // long lists: the wavefront walks them one vertex at a time
@@ -1488,7 +1492,7 @@ GG_ROUND_KERNEL(8) void k_bfs_diropt(Round R) {
                 const int ob = __shfl(ib, o, 64), oe = __shfl(ie, o, 64);
                 bool hit = false;
                 for (int e = ob; e < oe && !hit; e += 64) {
-                    const bool h = e + lane < oe && val[icol[e + lane]] == lev;
+                    const bool h = e + lane < oe && on_level(icol[e + lane]);
                     if (e + lane < oe) acc.e++;
                     hit = __ballot(h) != 0;
                 }
@@ -1503,6 +1507,27 @@ GG_ROUND_KERNEL(8) void k_bfs_diropt(Round R) {
         }
     }
     block_finish(R, acc, R.r % 3, KIND_ROUND);
+}
+
+// The frontier of round R.r as a bit per vertex in the round's heavy-row bitmap
+// (a pulled round marks no heavy row, and the next round clears the bitmap),
+// if the round pulls: launched after round R.r - 1.
+__global__ __launch_bounds__(256) void k_front_bits(Round R) {
+    if (*(volatile int*)&R.ws.ctl->done || prev_front(R) * kPullRatio <= R.g.n) return;
+    const int words = (R.g.n + 31) / 32;
+    const int tt = gridDim.x * blockDim.x;
+    const uint4* vf = reinterpret_cast<const uint4*>(R.ws.vflag[R.r & 1]);
+    unsigned* bits = R.ws.hbits[R.r & 1];
+    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < words; i += tt) {
+        // the flags are bytes of 0 or 1, padded to whole groups: four of them
+        // times 0x01020408 collect in bits 24..27
+        const uint4 a = vf[2 * (long long)i], b = vf[2 * (long long)i + 1];
+        const unsigned x[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+        unsigned w = 0;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) w |= ((x[k] * 0x01020408u >> 24) & 15u) << (4 * k);
+        bits[i] = w;
+    }
 }
 
 // Clear frontier generation `gen` (vertex and tile flags; the arrays are
@@ -2824,6 +2849,10 @@ hipError_t launch_heavy(const Round& R, int algo, int grid, int block, hipStream
 
 hipError_t launch_bfs_diropt(const Round& R, int grid, int block, hipStream_t s) {
     GG_LAUNCH(k_bfs_diropt, grid, block, s, R);
+}
+
+hipError_t launch_front_bits(const Round& R, int grid, int block, hipStream_t s) {
+    GG_LAUNCH(k_front_bits, grid, block, s, R);
 }
 
 hipError_t launch_cc_diropt(const Round& R, int grid, int block, hipStream_t s) {
