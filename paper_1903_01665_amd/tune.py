@@ -38,6 +38,8 @@ NEARFAR = ([(V, NF, BAL, de, 0, 0) for de in (8, 16, 32, 64, 128, 512)] +
            # long chains of passes (deep graphs) and finer widths around them
            [(V, NF, BAL, de, 64, 0) for de in (24, 32, 48)] +
            [(V, NF, BAL, de, 32, 0) for de in (24, 48)] +
+           # buckets below the mean weight (large uniform graphs)
+           [(V, NF, BAL, de, h, 0) for de in (3, 4, 6) for h in (8, 32)] +
            # narrow buckets that hold back only long rows (skewed graphs)
            [(V, NF, BAL, de, 4, far) for de in (2, 3, 4, 6) for far in (32, 96)])
 DIROPT = [(V, gg.DIROPT, BAL, 0, 0, 0)]
@@ -53,7 +55,9 @@ SSSP_DIROPT = [(V, gg.DIROPT, BAL, 0, 0, 0)]
 CALIB_STREAM = 0xCA11B
 CALIBRATION = [("rmat", 12), ("rmat", 16), ("rmat", 20), ("rmat", 21), ("rmat", 22),
                ("er", 14), ("er", 18), ("er", 22), ("er", 23),
-               ("grid", 128), ("grid", 512), ("grid", 2048), ("grid", 4100)]
+               ("grid", 128), ("grid", 512), ("grid", 2048), ("grid", 4100),
+               # the classes between (an earlier table's measurements end before them)
+               ("rmat", 18), ("er", 20), ("grid", 1024)]
 
 
 def make(kind, p, seed):
@@ -156,7 +160,7 @@ def measure(args, known=None):
         avg_w = float(hg.w.mean()) if hg.w is not None and hg.m else 1.0
         for algo in ALGOS:
             times = {}
-            if known:
+            if known and len(results) < len(known):
                 ka, kc, kt = known[len(results)]
                 if (ka, tuple(kc)) != (algo, tuple(cls)):
                     raise RuntimeError(f"measurements do not match: {ka} {kc} vs {algo} {cls}")
