@@ -29,6 +29,7 @@
 // that a second kernel of the same round spreads over the whole grid.
 
 #include <algorithm>
+#include <atomic>
 
 #include "gg_internal.h"
 
@@ -2899,18 +2900,22 @@ hipError_t launch_small(const Round& R, int algo, int max_n, long long max_m, hi
                     : algo == SSSP ? reinterpret_cast<const void*>(k_small<SSSP>)
                                    : reinterpret_cast<const void*>(k_small<BFS>);
     const size_t lds = small_lds(algo, max_n, max_m);
-    static const hipError_t allowed = [] {
+    // more LDS than the default limit is asked for once on every device
+    static std::atomic<unsigned long long> allowed{0};
+    int dev = 0;
+    hipError_t err = hipGetDevice(&dev);
+    if (err != hipSuccess) return err;
+    const unsigned long long bit = 1ull << (dev & 63);
+    if (!(allowed.load(std::memory_order_acquire) & bit)) {
         const int most = (int)std::max(small_lds(SSSP, kSmallN, kSmallM), small_lds(CC, kSmallN, 0));
         for (const void* k : {reinterpret_cast<const void*>(k_small_cc),
                               reinterpret_cast<const void*>(k_small<SSSP>),
                               reinterpret_cast<const void*>(k_small<BFS>)}) {
-            const hipError_t e =
-                hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, most);
-            if (e != hipSuccess) return e;
+            err = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, most);
+            if (err != hipSuccess) return err;
         }
-        return hipSuccess;
-    }();
-    if (allowed != hipSuccess) return allowed;
+        allowed.fetch_or(bit, std::memory_order_release);
+    }
     const int grid = R.inst ? (R.nsrc < kMaxStatBlocks ? R.nsrc : kMaxStatBlocks) : 1;
     Round arg = R;
     void* args[] = {&arg};
