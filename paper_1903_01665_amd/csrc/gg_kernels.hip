@@ -265,6 +265,18 @@ __device__ __forceinline__ void wave_rows_balanced(int beg, int deg, int sv, F&&
 
 // ---------------------------------------------------------- algorithms ----
 
+// Waits for the loads of x here.  Loads under a lane mask are followed by a
+// join where the compiler no longer knows how many are in flight, so each
+// later use inside a branch of its own waits for everything outstanding --
+// also the gathers, stores and atomics of the branches before it, which then
+// run one after another (4096 x 4096 grid, SSSP: 19.95 ms so, 18.96 with the
+// waits here; worklist on an R-MAT graph of 2^18 vertices 464 and 432 us).
+template <int U>
+__device__ __forceinline__ void landed(int (&x)[U]) {
+#pragma unroll
+    for (int j = 0; j < U; ++j) asm volatile("" : "+v"(x[j]));
+}
+
 // Relax one edge e (p -> t = col[e]) with the tail's value sv.  Returns true
 // when this lane lowered val[t] (the caller pushes t or counts an update).
 template <int A>
@@ -296,18 +308,6 @@ __device__ __forceinline__ bool relax_edge(const Round& R, const int* col, int e
         }
         return false;
     }
-}
-
-// Waits for the loads of x here.  Loads under a lane mask are followed by a
-// join where the compiler no longer knows how many are in flight, so each
-// later use inside a branch of its own waits for everything outstanding --
-// also the gathers, stores and atomics of the branches before it, which then
-// run one after another (4096 x 4096 grid, SSSP: 19.95 ms so, 18.96 with the
-// waits here; worklist on an R-MAT graph of 2^18 vertices 464 and 432 us).
-template <int U>
-__device__ __forceinline__ void landed(int (&x)[U]) {
-#pragma unroll
-    for (int j = 0; j < U; ++j) asm volatile("" : "+v"(x[j]));
 }
 
 // Relax U edges per lane with the loads of all of them in flight before the
@@ -859,18 +859,24 @@ __device__ __forceinline__ void edge_sync_four(const Round& R, const int* src, c
         int vu[4], vt[4];
 #pragma unroll
         for (int j = 0; j < 4; ++j) vu[j] = val[u[j]];
+        landed(vu);
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const bool need = A == SSSP ? vu[j] != kInf : A == BFS ? vu[j] == R.r : true;
             vt[j] = need ? val[t[j]] : 0;
         }
+        landed(vt);
         acc.e += 4;
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             if (A == SSSP) {
                 if (vu[j] == kInf) continue;
                 const unsigned cand = (unsigned)vu[j] + (unsigned)wt[j];
-                if (cand < (unsigned)vt[j] && (int)cand < atomicMin(&val[t[j]], (int)cand)) acc.u++;
+                // the loads decide, as in relax_batch: no returned value to wait for
+                if (cand < (unsigned)vt[j]) {
+                    atomicMin(&val[t[j]], (int)cand);
+                    acc.u++;
+                }
             } else if (A == BFS) {
                 if (vu[j] == R.r && vt[j] > R.r + 1) {
                     val[t[j]] = R.r + 1;
@@ -1488,20 +1494,26 @@ GG_ROUND_KERNEL(8) void k_bfs_diropt(Round R) {
             }
             const int* icol = g.symmetric ? g.col : g.scol;
             const unsigned* fb = R.front_bits ? R.ws.hbits[cur] : nullptr;
-            auto on_level = [&](int u) {
-                return fb ? ((fb[u >> 5] >> (u & 31)) & 1u) != 0 : val[u] == lev;
-            };
+            auto word = [&](int u) { return fb ? (int)fb[u >> 5] : val[u]; };
+            auto on_level = [&](int u, int x) { return fb ? ((x >> (u & 31)) & 1) != 0 : x == lev; };
             bool found = false;
-            // short lists: each lane walks its own, kBatch entries at a time
+            // short lists: each lane walks its own, kBatch entries at a time, all of
+            // their gathers in flight (see landed; the three traversals of a uniform
+            // graph of 2^26 edges 4.44 ms with one at a time, 4.35 so)
             const bool shortl = todo && ie - ib <= 64;
             for (int e = ib; shortl && !found && e < ie; e += kBatch) {
-                bool x[kBatch];
+                int u[kBatch], x[kBatch];
 #pragma unroll
-                for (int j = 0; j < kBatch; ++j) x[j] = e + j < ie && on_level(icol[e + j]);
+                for (int j = 0; j < kBatch; ++j) u[j] = e + j < ie ? icol[e + j] : -1;
+                landed(u);
+#pragma unroll
+                for (int j = 0; j < kBatch; ++j) x[j] = u[j] >= 0 ? word(u[j]) : 0;
+                landed(x);
 #pragma unroll
                 for (int j = 0; j < kBatch; ++j) {
-                    if (e + j < ie) acc.e++;
-                    found |= x[j];
+                    if (u[j] < 0) continue;
+                    acc.e++;
+                    found |= on_level(u[j], x[j]);
                 }
             }
             // long lists: the wavefront walks them one vertex at a time
@@ -1512,8 +1524,12 @@ GG_ROUND_KERNEL(8) void k_bfs_diropt(Round R) {
                 const int ob = __shfl(ib, o, 64), oe = __shfl(ie, o, 64);
                 bool hit = false;
                 for (int e = ob; e < oe && !hit; e += 64) {
-                    const bool h = e + lane < oe && on_level(icol[e + lane]);
-                    if (e + lane < oe) acc.e++;
+                    bool h = false;
+                    if (e + lane < oe) {
+                        const int u = icol[e + lane];
+                        h = on_level(u, word(u));
+                        acc.e++;
+                    }
                     hit = __ballot(h) != 0;
                 }
                 if (lane == o) found = hit;
