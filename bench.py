@@ -85,9 +85,9 @@ def algorithmic_bytes(algo, mode, sched, kind, n, prof_kind, launches):
     U = prof_kind["updates"]
     P = prof_kind["pushes"]
     if sched == 5 and kind == "round":
-        # union-find: the row offsets of every vertex per linking phase, per
-        # linked edge its column, the two roots found and the swap
-        return 8 * n * launches + 16 * E
+        # union-find: the row offsets of every vertex in the first and the
+        # last phase, the column of every edge looked at, the parents stored
+        return 8 * n * min(launches, 2) + 4 * E + 4 * U
     per_edge = 12 if algo == "sssp" else 8
     if sched == 4 and (algo == "sssp" or (algo == "cc" and mode == 0)):
         # per-round push/pull (SSSP; CC in vertex mode): an edge is 12 B
@@ -118,6 +118,8 @@ def algorithmic_bytes(algo, mode, sched, kind, n, prof_kind, launches):
         return ntiles * launches + 16 * V + per_edge * E + extra + 2 * P
     if kind == "heavy":
         return per_edge * E + 2 * P
+    if algo == "bfs" and sched == 4:  # the bits of a level: 4 B and a bit per vertex
+        return 4 * n + (4 * n + n // 8) * max(0, launches - 1)
     return (4 + (2 if sched == 1 else 0)) * n + 8 * n * max(0, launches - 1)
 
 
@@ -126,7 +128,8 @@ def kernel_symbol(algo, kind, mode, sched, mapping, hops=0):
     the variant launches no kernel of that kind)."""
     a = {"sssp": 0, "bfs": 1, "cc": 2}[algo]
     if sched == 5:  # union-find CC: linking rounds and compressions, no chunk kernel
-        return {"round": "gg::k_uf(gg::Round)", "aux": "gg::k_uf_compress(gg::Round)"}.get(kind)
+        return {"round": "gg::k_uf(gg::Round)",
+                "aux": "void gg::k_uf_compress<false>(gg::Round, int)"}.get(kind)
     if kind == "heavy":
         return f"void gg::k_heavy<{a}>(gg::Round)"
     if kind == "aux":
