@@ -710,6 +710,8 @@ hipError_t plan_round(Plan& p, int r) {
                         [&] { return launch_uf_hook(R, k, uf.share, p.g_round, kBlock, p.s); });
         if (e == hipSuccess) e = compress(k);
     }
+    if (e == hipSuccess && p.uf && r == 3 && p.g->n_shchunks > 0)
+        e = plan_launch(p, KIND_HEAVY, [&] { return launch_uf_long(R, p.g_round, kBlock, p.s); });
     if (e == hipSuccess && p.uf && (r == 0 || r == 3)) e = compress(-1);
     return e;
 }

@@ -2451,10 +2451,10 @@ __global__ __launch_bounds__(256) void k_t_fill(const int* col, const int* w, co
 // vertices without a smaller neighbour among those.  Round 1 hooks the roots
 // under smaller neighbouring trees, by plain stores too (k_uf_hook).  Round 2
 // samples the roots of 1024 vertices and takes the most frequent as the giant
-// component's; round 3 links, for every vertex outside that component, all its
-// neighbours (an edge with one end in the giant component is seen from the
-// other end; edges inside it need nothing), hanging the larger of two roots
-// under the smaller with a compare-and-swap.  Every step but the sampling is
+// component's; round 3 (k_uf_rest, k_uf_long) links, for every vertex outside that
+// component, all its neighbours (an edge with one end in the giant component is
+// seen from the other end; edges inside it need nothing), hanging the larger of
+// two roots under the smaller with a compare-and-swap.  Every step but the sampling is
 // followed by a compression with path halving (every vertex walks, so a long
 // chain is halved by all of its vertices at once), the last by one in which
 // every vertex writes only its own root.  A parent is always a smaller id of
@@ -2502,6 +2502,28 @@ __device__ __forceinline__ bool uf_link(int* parent, int a, int b) {
                                                  __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
             return true;
     }
+}
+
+// Link a vertex whose parent was pv with kBatch neighbours, col[0], col[step], ...
+// of the `left` that remain.  A neighbour whose parent was pv too is in the
+// tree already, which a gather shows without a search.  (Trees are flat here, so
+// the searches of a tree all read its root, one after another: round 3 of a path
+// of 2^21 shuffled ids took 5.1 ms when every edge searched, 0.1 so.)
+__device__ __forceinline__ void uf_link_batch(int* parent, const int* col, int left, int step,
+                                              int pv, Acc& acc) {
+    int x[kBatch];
+#pragma unroll
+    for (int j = 0; j < kBatch; ++j) x[j] = j * step < left ? col[j * step] : -1;
+    landed(x);
+#pragma unroll
+    for (int j = 0; j < kBatch; ++j) {
+        acc.e += x[j] >= 0;
+        x[j] = x[j] >= 0 ? parent[x[j]] : pv;
+    }
+    landed(x);
+#pragma unroll
+    for (int j = 0; j < kBatch; ++j)
+        if (x[j] != pv) acc.u += uf_link(parent, pv, x[j]);
 }
 
 __global__ __launch_bounds__(256) void k_uf(Round R) {
@@ -2558,22 +2580,64 @@ __global__ __launch_bounds__(256) void k_uf(Round R) {
             __syncthreads();
             if (threadIdx.x == 0) R.ws.ctl->giant = kInf - (int)(s_best & 0xffffffffu);
         }
-    } else if (R.r == 3) {
-        const int giant = *(volatile int*)&R.ws.ctl->giant;
-        for (long long v = tid; v < g.n; v += tt) {
-            if (parent[v] == giant) continue;
-            const int b = g.srow[v], e1 = g.srow[v + 1];
-            for (int e = b; e < e1; ++e) {
-                acc.e++;
-                acc.u += uf_link(parent, (int)v, g.scol[e]);
-            }
-        }
     }
-    // phases 0-2 keep the traversal going (one push on the books); the
-    // last one changes nothing the next round would read
-    if (R.r < 3) acc.p = tid == 0;
-    else acc.u = acc.p = 0;
+    // rounds 0-2 keep the traversal going (one push on the books)
+    acc.p = tid == 0;
     block_finish(R, acc, R.r % 3, KIND_ROUND);
+}
+
+// Round 3: the vertices outside the giant tree link their neighbours, those
+// with long rows through k_uf_long.  Nothing that the next round would read
+// changes, so that round ends the traversal.
+__global__ __launch_bounds__(256) void k_uf_rest(Round R) {
+    if (!round_begin(R)) return;
+    const DevGraph& g = R.g;
+    int* parent = R.val;
+    const long long tid = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    const long long tt = (long long)gridDim.x * blockDim.x;
+    const int giant = *(volatile int*)&R.ws.ctl->giant;
+    bool long_rows = false;
+    Acc acc;
+    for (long long v = tid; v < g.n; v += tt) {
+        const int pv = parent[v];
+        if (pv == giant) continue;
+        const int b = g.srow[v], deg = g.srow[v + 1] - b;
+        if (deg > g.heavy) {
+            long_rows = true;
+            continue;
+        }
+        for (int k = 0; k < deg; k += kBatch)
+            uf_link_batch(parent, g.scol + b + k, deg - k, 1, pv, acc);
+    }
+    if (__syncthreads_or(long_rows) && threadIdx.x == 0) R.ws.ctl->hooked[kUfLong] = 1;
+    acc.u = 0;
+    block_finish(R, acc, R.r % 3, KIND_ROUND);
+}
+
+// Round 3, the rows longer than the heavy threshold outside the giant tree: a
+// wavefront per chunk.  (On one lane their neighbours are searched one after
+// another: two R-MAT graphs of 2^20 vertices and 2^23 edges side by side 47 ms,
+// so 0.30, by edge sweeps 0.62; stars of 1024 leaves, 2^20 vertices, 1.14 and 0.18.)
+__global__ __launch_bounds__(256) void k_uf_long(Round R) {
+    Ctl* ctl = R.ws.ctl;
+    if (*(volatile int*)&ctl->done || !*(volatile int*)&ctl->hooked[kUfLong]) return;
+    const DevGraph& g = R.g;
+    int* parent = R.val;
+    const int giant = *(volatile int*)&ctl->giant;
+    const int lane = threadIdx.x & 63;
+    const long long gw = ((long long)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
+    const long long tw = (long long)gridDim.x * blockDim.x >> 6;
+    Acc acc;
+    for (long long k = gw; k < g.n_shchunks; k += tw) {
+        const int2 c = g.shchunks[k];
+        const int pv = parent[c.x];
+        if (pv == giant) continue;
+        const int len = min(g.chunk, g.srow[c.x + 1] - c.y);
+        for (int e = lane; e < len; e += 64 * kBatch)
+            uf_link_batch(parent, g.scol + c.y + e, len - e, 64, pv, acc);
+    }
+    acc.u = 0;
+    block_finish(R, acc, R.r % 3, KIND_AUX);
 }
 
 // Round 1, pass `pass`.  Pass 0: every root takes the smallest parent that its
@@ -2904,6 +2968,7 @@ __global__ __launch_bounds__(64) void k_mark(unsigned long long* p, unsigned lon
 }
 
 hipError_t launch_uf(const Round& R, int grid, int block, hipStream_t s) {
+    if (R.r == 3) GG_LAUNCH(k_uf_rest, grid, block, s, R);
     GG_LAUNCH(k_uf, grid, block, s, R);
 }
 
@@ -2911,6 +2976,10 @@ hipError_t launch_uf_hook(const Round& R, int pass, int share, int grid, int blo
                           hipStream_t s) {
     if (pass == 0) GG_LAUNCH(k_uf_hook<true>, grid, block, s, R, pass, 1, 0);
     GG_LAUNCH(k_uf_hook<false>, grid, block, s, R, pass, share, (pass - 1) % share);
+}
+
+hipError_t launch_uf_long(const Round& R, int grid, int block, hipStream_t s) {
+    GG_LAUNCH(k_uf_long, grid, block, s, R);
 }
 
 hipError_t launch_uf_double(const Round& R, int grid, int block, hipStream_t s) {
