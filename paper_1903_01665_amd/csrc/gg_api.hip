@@ -694,16 +694,12 @@ hipError_t plan_round(Plan& p, int r) {
         const int gb = std::max(1, std::min(p.g_round, (words + 4 * kBlock - 1) / (4 * kBlock)));
         e = plan_launch(p, KIND_AUX, [&] { return launch_front_bits(next, gb, kBlock, p.s); });
     }
-    // union-find: the chains of a deep graph, the hooking passes of round 1,
-    // and a compression after each step but the sampling
+    // union-find: the hooking passes of round 1, the long rows of round 3, and a
+    // compression after each step but the sampling
     auto compress = [&](int pass) {
         return plan_launch(p, KIND_AUX,
                            [&] { return launch_uf_compress(R, pass, p.g_round, kBlock, p.s); });
     };
-    if (p.uf && r == 0 && p.g->levels >= 256)
-        for (int k = 0; k < kUfDoubles && e == hipSuccess; ++k)
-            e = plan_launch(p, KIND_AUX,
-                            [&] { return launch_uf_double(R, p.g_round, kBlock, p.s); });
     const UfPlan uf = uf_plan(p.g->n, p.g->ms);
     for (int k = 0; p.uf && r == 1 && k < uf.passes && e == hipSuccess; ++k) {
         e = plan_launch(p, KIND_AUX,
@@ -711,7 +707,7 @@ hipError_t plan_round(Plan& p, int r) {
         if (e == hipSuccess) e = compress(k);
     }
     if (e == hipSuccess && p.uf && r == 3 && p.g->n_shchunks > 0)
-        e = plan_launch(p, KIND_HEAVY, [&] { return launch_uf_long(R, p.g_round, kBlock, p.s); });
+        e = plan_launch(p, KIND_AUX, [&] { return launch_uf_long(R, p.g_round, kBlock, p.s); });
     if (e == hipSuccess && p.uf && (r == 0 || r == 3)) e = compress(-1);
     return e;
 }

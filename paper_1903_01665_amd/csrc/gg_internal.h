@@ -37,7 +37,7 @@ inline UfPlan uf_plan(long long n, long long ms) {
     return UfPlan{ms >= 3 * n ? 3 : 5, 1};
 }
 constexpr int kUfLong = 7;
-constexpr int kUfDoubles = 3;        // its passes over the chains of a deep graph
+constexpr int kUfSteps = 16;         // steps of a compression's walks but in the last
 constexpr int kXcd = 8;              // accelerator dies; workgroups go to them round-robin
 // Tiles per frontier work item, as a shift: the most (up to kItemTiles) that
 // still leave an item for each of kFillWaves wavefronts.  Graphs of 4M
@@ -116,6 +116,7 @@ struct Ctl {
     int giant;       // CC by union-find: the root most sampled vertices have
     int hooked[8];   // ... and whether its hooking pass [k] hooked anything; [kUfLong]:
                      // round 3 left long rows to k_uf_long
+    int left[8];     // [k]: the compression before hooking pass [k] left a chain
 };
 
 // Per-block counters, summed on the host after a traversal; one array of
@@ -223,13 +224,11 @@ hipError_t launch_cc_diropt(const Round& R, int grid, int block, hipStream_t s);
 hipError_t launch_sssp_diropt(const Round& R, int grid, int block, hipStream_t s);
 // CC by union-find (GG_UNIONFIND), round R.r: join, nothing, find the giant
 // root, link the rest; the hooking passes of round 1; the long rows of
-// round 3 (graphs with heavy-row chunks); the kUfDoubles passes after round 0 on
-// a deep graph; and the compression after each
+// round 3 (graphs with heavy-row chunks); and the compression after each
 hipError_t launch_uf(const Round& R, int grid, int block, hipStream_t s);
 hipError_t launch_uf_hook(const Round& R, int pass, int share, int grid, int block,
                           hipStream_t s);
 hipError_t launch_uf_long(const Round& R, int grid, int block, hipStream_t s);
-hipError_t launch_uf_double(const Round& R, int grid, int block, hipStream_t s);
 // pass: the hooking pass before it (-1: none)
 hipError_t launch_uf_compress(const Round& R, int pass, int grid, int block, hipStream_t s);
 // A whole traversal of a graph of at most kSmallN vertices (or, with R.inst,

@@ -2455,9 +2455,8 @@ __global__ __launch_bounds__(256) void k_t_fill(const int* col, const int* w, co
 // component, all its neighbours (an edge with one end in the giant component is
 // seen from the other end; edges inside it need nothing), hanging the larger of
 // two roots under the smaller with a compare-and-swap.  Every step but the sampling is
-// followed by a compression with path halving (every vertex walks, so a long
-// chain is halved by all of its vertices at once), the last by one in which
-// every vertex writes only its own root.  A parent is always a smaller id of
+// followed by a compression with path halving, the last by one in which every
+// vertex writes only its own root.  A parent is always a smaller id of
 // the same component, so a root is the smallest id of its tree, and the parent
 // array ends as the smallest id of each component -- the labels of the other
 // schedules.  The value array is the parent array (labels start as the ids).
@@ -2643,7 +2642,7 @@ __global__ __launch_bounds__(256) void k_uf_long(Round R) {
 // Round 1, pass `pass`.  Pass 0: every root takes the smallest parent that its
 // first neighbours have.  The roots it leaves have mostly neighbours of their
 // own tree, so the later passes look from one vertex in `share` (another
-// each pass), which hooks its parent, a root after the compression.  Several
+// each pass), which hooks its parent if that is a root.  Several
 // vertices may hook one root; the last store stands, and a join that is lost
 // so is found again in round 3 unless both its trees are in the giant one.
 // After a pass from the vertices that hooked nothing the rest return at once.
@@ -2669,7 +2668,7 @@ __global__ __launch_bounds__(256) void k_uf_hook(Round R, int pass, int share, i
         for (int k = 0; k < K; ++k) x[k] = parent[x[k]];
 #pragma unroll
         for (int k = 0; k < K; ++k) least = min(least, x[k]);
-        if (least < r) {
+        if (least < r && (ROOTS || parent[r] == r)) {
             parent[r] = least;
             hooked = true;
         }
@@ -2677,28 +2676,23 @@ __global__ __launch_bounds__(256) void k_uf_hook(Round R, int pass, int share, i
     if (__syncthreads_or(hooked) && threadIdx.x == 0) ctl->hooked[pass] = 1;
 }
 
-// Every vertex two parents higher.  On a deep graph round 0 leaves chains as
-// long as the graph is deep (a 4096 x 4096 grid: a chain per column), which
-// the walks of the compression below climb slowly: all of CC 2.06 ms, with
-// kUfDoubles of these passes first 0.78 ms.
-__global__ __launch_bounds__(256) void k_uf_double(Round R) {
-    if (*(volatile int*)&R.ws.ctl->done) return;
-    int* parent = R.val;
-    const long long tid = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    const long long tt = (long long)gridDim.x * blockDim.x;
-    for (long long v = tid; v < R.g.n; v += tt) {
-        const int p = parent[v], x = parent[p], y = parent[x];
-        if (y != p) parent[v] = y;
-    }
-}
-
-// Every parent to its root.  LAST: each thread writes its own vertex only (a
-// halving store can land after the owner's own and leave an ancestor that is
-// not the root).
+// Every parent to its root, or kUfSteps of its walk up the way: round 0 leaves
+// chains as long as the graph is deep (a 4096 x 4096 grid: a chain per column; a
+// path: one in all), whose walks are short only if the vertices above have been
+// hung higher by then, which the dies' caches do not show within a launch.  The
+// chains that a pass leaves are 1/kUfSteps as long or less, and the next
+// compression runs for them.  A path of 2^21 vertices: walks to the end 2.34 ms,
+// of 16 steps 0.19, of 32 0.22; the grid 0.70 (0.58 with three passes before them
+// that hang every vertex two parents higher), 0.48 and 0.53.
+// LAST: each thread writes its own vertex only (a halving store can land after
+// the owner's own and leave an ancestor that is not the root).
 template <bool LAST>
 __global__ __launch_bounds__(256) void k_uf_compress(Round R, int pass) {
-    if (*(volatile int*)&R.ws.ctl->done || (pass >= 0 && !*(volatile int*)&R.ws.ctl->hooked[pass]))
+    Ctl* ctl = R.ws.ctl;
+    if (*(volatile int*)&ctl->done ||
+        (pass >= 0 && !*(volatile int*)&ctl->hooked[pass] && !*(volatile int*)&ctl->left[pass]))
         return;
+    bool left = false;
     int* parent = R.val;
     const long long tid = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     const long long tt = (long long)gridDim.x * blockDim.x;
@@ -2716,15 +2710,17 @@ __global__ __launch_bounds__(256) void k_uf_compress(Round R, int pass) {
             // y's parent x differs from y: hang v, then every vertex met,
             // two steps higher
             int at = (int)v;
-            while (x != y) {
+            for (int k = 0; x != y && k < kUfSteps; ++k) {
                 parent[at] = x;
                 at = x;
                 y = parent[at];
                 x = parent[y];
             }
             parent[v] = y;
+            left |= x != y;
         }
     }
+    if (!LAST && __syncthreads_or(left) && threadIdx.x == 0) ctl->left[pass + 1] = 1;
 }
 
 // ------------------------------------------------------- renumbering ----
@@ -2980,10 +2976,6 @@ hipError_t launch_uf_hook(const Round& R, int pass, int share, int grid, int blo
 
 hipError_t launch_uf_long(const Round& R, int grid, int block, hipStream_t s) {
     GG_LAUNCH(k_uf_long, grid, block, s, R);
-}
-
-hipError_t launch_uf_double(const Round& R, int grid, int block, hipStream_t s) {
-    GG_LAUNCH(k_uf_double, grid, block, s, R);
 }
 
 hipError_t launch_uf_compress(const Round& R, int pass, int grid, int block, hipStream_t s) {

@@ -78,7 +78,7 @@ def best_ms(f):
     return 1e3 * min(times)
 
 
-@pytest.mark.parametrize("shape", ["skewed", "shuffled-chain"])
+@pytest.mark.parametrize("shape", ["skewed", "chain", "shuffled-chain"])
 def test_cc_has_no_serial_path(shape):
     """Edge sweeps take a few passes on the skewed graph; the passes over a chain
     are gathers of its parents, tens of microseconds each."""
