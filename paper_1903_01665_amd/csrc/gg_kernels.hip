@@ -2183,12 +2183,13 @@ __global__ __launch_bounds__(kSmallBlock) void k_small_cc(Round R) {
 #pragma unroll
         for (int j = 0; j < kBatch; ++j) {
             const int e = e0 + j * kSmallBlock;
-            u[j] = e < g.m ? g.src[e] : 0;
-            v[j] = e < g.m ? g.col[e] : 0;
+            u[j] = e < g.m ? g.src[e] : -1;
+            v[j] = e < g.m ? g.col[e] : -1;
         }
 #pragma unroll
         for (int j = 0; j < kBatch; ++j) {
             int a = u[j], b = v[j];
+            if (a < 0) continue;
             acc.e++;
             for (;;) {
                 a = find(a);
