@@ -20,3 +20,31 @@ def test_cc_counts_each_edge_once(m):
         assert g.stats()["edges_processed"] == m
     finally:
         g.free()
+
+
+@pytest.mark.parametrize("order", ["up", "down", "shuffled"])
+def test_cc_of_a_chain(order):
+    """The links of a path in order make one chain; no lane walks all of it
+    (32,767 dependent reads of LDS take more than a millisecond)."""
+    import time
+
+    import torch
+
+    from paper_1903_01665_amd import gg
+    p = np.arange(32768, dtype=np.int32)
+    p = {"up": p, "down": p[::-1], "shuffled": np.random.default_rng(4).permutation(p)}[order]
+    hg = gen.from_edges(len(p), p[:-1], p[1:], np.ones(len(p) - 1, np.int32), name=order)
+    for renumber in (None, True):
+        g = gg.Graph.from_host(hg, renumber=renumber)
+        try:
+            times = []
+            for _ in range(6):
+                t = time.perf_counter()
+                c = g.cc()
+                torch.cuda.synchronize()
+                times.append(1e3 * (time.perf_counter() - t))
+                assert int(c.max()) == 0
+            print(order, renumber, times, flush=True)
+            assert min(times) < 0.7
+        finally:
+            g.free()
