@@ -609,7 +609,7 @@ int plan_make(gg_graph g, gg_ws ws, int algo, int source, const int* sources_dev
     // ... and the shortcut kernel of a CC pull round
     if (diropt && p.cc && R.pullmode) p.need_jump = true;
     p.g_jump = grid((n + kBlock - 1) / kBlock);
-    R.front_bits = diropt && algo == GG_ALGO_BFS && !g->renumbered && n >= kFrontBitsN;
+    p.front_bits = diropt && algo == GG_ALGO_BFS && !g->renumbered && n >= kFrontBitsN;
     return GG_OK;
 }
 
@@ -666,6 +666,7 @@ hipError_t plan_init(Plan& p) {
 hipError_t plan_round(Plan& p, int r) {
     Round& R = p.R;
     R.r = r;
+    R.front_bits = p.front_bits && r < kFrontBitsRounds;
     if (p.whole) {
         if (r > 0) return hipSuccess;
         const int max_n = R.inst ? p.g->inst_max_n : p.g->n;
@@ -687,7 +688,7 @@ hipError_t plan_round(Plan& p, int r) {
         e = plan_launch(p, KIND_HEAVY, [&] { return launch_heavy(R, p.algo, p.g_heavy, kBlock, p.s); });
     if (e == hipSuccess && p.need_jump)
         e = plan_launch(p, KIND_AUX, [&] { return launch_jump(R, p.g_jump, kBlock, p.s); });
-    if (e == hipSuccess && R.front_bits) {
+    if (e == hipSuccess && p.front_bits && r + 1 < kFrontBitsRounds) {
         Round next = R;
         next.r = r + 1;
         const int words = (R.g.n + 31) / 32;

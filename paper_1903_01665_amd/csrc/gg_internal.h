@@ -93,8 +93,11 @@ inline size_t small_lds(int algo, int n, long long m) {
 // costs ~3 us a round whether it pulls or not.  Uniform graphs: 2^23 vertices and
 // 2^26 edges 1.17 -> 0.84 ms, 2^22 and 2^25 0.92 -> 0.58, 2^21 and 2^24 0.44 ->
 // 0.34 (values of 8 MB); a renumbered R-MAT graph gathers its hot values at
-// 200 G/s as they are.
+// 200 G/s as they are.  Graphs with wide levels are shallow: later rounds than
+// the first kFrontBitsRounds look the values up, without the launch (a 1500 x 1500
+// grid, whose 3000 rounds never pull: 32.9 ms so, 44.5 with it in all of them).
 constexpr int kFrontBitsN = 1 << 21;
+constexpr int kFrontBitsRounds = 32;
 
 enum Kind { KIND_ROUND = 0, KIND_HEAVY = 1, KIND_AUX = 2 };
 

@@ -205,6 +205,7 @@ struct Plan {
     Round R{};
     bool async = false, edge = false, cc = false, diropt = false, uf = false;
     bool need_heavy = false, need_jump = false, prof = false;
+    bool front_bits = false;  // the first rounds' frontiers are made into bits
     // the whole traversal is one launch (round 0; there is no init kernel)
     bool whole = false;
     // renumbered graph: R.val is the workspace's array; the finishing
