@@ -861,15 +861,44 @@ int drive_step(Drive& d) {
     return 0;
 }
 
+// The calling thread between two looks at the pinned words.  It spins while
+// rounds of the usual length pass; then it gives the core up, and asks every
+// millisecond whether the stream has failed: a kernel that the device stopped
+// never reports.
+struct DriveWait {
+    long long r = -1;  // rounds enqueued at the last progress
+    std::chrono::steady_clock::time_point since, asked;
+};
+
+static int drive_wait(Drive& d, DriveWait& w) {
+    using std::chrono::microseconds;
+    const auto now = std::chrono::steady_clock::now();
+    if (d.r != w.r) w = DriveWait{d.r, now, now};
+    if (now - w.since < microseconds(200)) {
+        __builtin_ia32_pause();
+        return GG_OK;
+    }
+    if (now - w.asked >= microseconds(1000)) {
+        w.asked = now;
+        const hipError_t e = hipStreamQuery(d.p.s);
+        if (e == hipErrorNotReady) (void)hipGetLastError();
+        else HIPCHK(d.p.g, e);
+    }
+    if (now - w.since < microseconds(2000)) std::this_thread::yield();
+    else std::this_thread::sleep_for(microseconds(20));
+    return GG_OK;
+}
+
 // Blocking form: run the state machine to the end.
 int plan_drive(Plan& p, long long r0, int stamp_base, int tag, long long* r_end) {
     Drive d;
+    DriveWait w;
     d.p = p;
     int rc = drive_start(d, r0, stamp_base, tag);
     while (rc == GG_OK) {
         rc = drive_step(d);
-        if (rc == 1) break;
-        __builtin_ia32_pause();
+        if (rc == GG_OK) rc = drive_wait(d, w);
+        else break;
     }
     *r_end = d.r;
     if (rc < 0) return rc;
