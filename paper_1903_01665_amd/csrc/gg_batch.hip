@@ -133,7 +133,15 @@ int gg_batch_create(const gg_instance* inst, int32_t count, uint32_t flags, void
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     // group key: algorithm and graph class (size, skew) of the instance; the
     // instances that fit a workgroup form one group per algorithm, which runs
-    // as one launch with a workgroup each
+    // as one launch with a workgroup each (unless that group is too large for a
+    // graph, while those of the classes may not be)
+    long long fit_n[2] = {0, 0}, fit_m[2] = {0, 0};
+    for (int i = 0; i < count; ++i)
+        if ((inst[i].algo == GG_ALGO_SSSP || inst[i].algo == GG_ALGO_BFS) &&
+            fits_workgroup(inst[i])) {
+            fit_n[inst[i].algo] += inst[i].n;
+            fit_m[inst[i].algo] += inst[i].m;
+        }
     std::map<std::tuple<int, int, int>, std::vector<int>> keys;
     for (int i = 0; i < count; ++i) {
         int md = 0;
@@ -141,7 +149,9 @@ int gg_batch_create(const gg_instance* inst, int32_t count, uint32_t flags, void
         int32_t sc = 0, kc = 0, dc = 0;
         gg_class_of(inst[i].m, inst[i].n, md, -1, &sc, &kc, &dc);
         if (flags & GG_BATCH_ONE_GROUP) sc = kc = 0;
-        else if (fits_workgroup(inst[i])) sc = kc = -1;
+        else if (fits_workgroup(inst[i]) && fit_n[inst[i].algo] < (1LL << 31) &&
+                 fit_m[inst[i].algo] < (1LL << 31))
+            sc = kc = -1;
         keys[std::make_tuple(inst[i].algo, sc, kc)].push_back(i);
     }
     gg_batch b = new (std::nothrow) gg_batch_s();
