@@ -567,7 +567,7 @@ int plan_make(gg_graph g, gg_ws ws, int algo, int source, const int* sources_dev
 
     if (whole_ok(g, algo, nsrc, opts)) {
         p.whole = true;
-        p.g_round = nsrc > 0 ? std::min(nsrc, kMaxStatBlocks) : 1;
+        p.g_round = nsrc > 0 ? std::min(nsrc, std::min(std::max(1, dv.cus), kMaxStatBlocks)) : 1;
         R.inst = nsrc > 0 ? g->inst : nullptr;
         return GG_OK;
     }
@@ -669,10 +669,9 @@ hipError_t plan_round(Plan& p, int r) {
     R.front_bits = p.front_bits && r < kFrontBitsRounds;
     if (p.whole) {
         if (r > 0) return hipSuccess;
-        const int max_n = R.inst ? p.g->inst_max_n : p.g->n;
-        const long long max_m = R.inst ? p.g->inst_max_m : p.g->m;
+        const size_t lds = R.inst ? p.g->inst_lds : small_lds(p.algo, p.g->n, p.g->m);
         return plan_launch(p, KIND_ROUND,
-                           [&] { return launch_small(R, p.algo, max_n, max_m, p.s); });
+                           [&] { return launch_small(R, p.algo, lds, p.g_round, p.s); });
     }
     hipError_t e = plan_launch(p, KIND_ROUND, [&] {
         if (p.uf) return launch_uf(R, p.g_round, kBlock, p.s);

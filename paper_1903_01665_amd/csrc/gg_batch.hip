@@ -212,23 +212,23 @@ int gg_batch_create(const gg_instance* inst, int32_t count, uint32_t flags, void
             hipHostMalloc(reinterpret_cast<void**>(&G.h_ctl), 2 * sizeof(int)) != hipSuccess)
             return bail(GG_EHIP);
         bool fit = true;
-        int max_n = 0;
-        long long max_m = 0;
-        for (int i : G.members) {
-            fit = fit && fits_workgroup(inst[i]);
-            max_n = std::max(max_n, inst[i].n);
-            max_m = std::max<long long>(max_m, inst[i].m);
-        }
+        for (int i : G.members) fit = fit && fits_workgroup(inst[i]);
         if (fit) {
-            std::vector<int> first(G.vbase.begin(), G.vbase.end());
-            first.push_back((int)G.n);
+            // the longest first, so that none of them starts last
+            std::vector<int4> first;
+            for (size_t k = 0; k < G.members.size(); ++k) {
+                const gg_instance& x = inst[G.members[k]];
+                const int vb = (int)G.vbase[k];
+                first.push_back(make_int4(vb, vb + x.n, vb + x.source, (int)x.m));
+                G.g->inst_lds = std::max(G.g->inst_lds, small_lds(G.algo, x.n, x.m));
+            }
+            std::stable_sort(first.begin(), first.end(),
+                             [](const int4& a, const int4& b) { return a.w > b.w; });
             if (dalloc(&G.g->inst, first.size()) != hipSuccess ||
-                hipMemcpyAsync(G.g->inst, first.data(), sizeof(int) * first.size(),
+                hipMemcpyAsync(G.g->inst, first.data(), sizeof(int4) * first.size(),
                                hipMemcpyHostToDevice, s) != hipSuccess ||
                 hipStreamSynchronize(s) != hipSuccess)
                 return bail(GG_EHIP);
-            G.g->inst_max_n = max_n;
-            G.g->inst_max_m = max_m;
         }
         gg_resolve(G.g, G.algo, nullptr, &G.opts);
         // The table's choice is measured on single-source traversals.  A

@@ -119,6 +119,7 @@ struct Ctl {
     int giant;       // CC by union-find: the root most sampled vertices have
     int hooked[8];   // ... and whether its hooking pass [k] hooked anything; [kUfLong]:
                      // round 3 left long rows to k_uf_long
+    int taken;       // batch of whole traversals: instances taken beyond a workgroup's first
     int left[8];     // [k]: the compression before hooking pass [k] left a chain
 };
 
@@ -202,8 +203,8 @@ struct Round {
                     // CC: the both-directions rows) instead of pushing or sweeping
     int direct_lists; // SSSP local expansion: list passes issue their atomics without a
                       // check load of the head value
-    const int* inst; // batch of whole traversals: first vertex of each instance and the
-                     // end of the last, [nsrc + 1] (null otherwise)
+    const int4* inst; // batch of whole traversals: first vertex, end, source and edges of
+                      // each instance, [nsrc] (null otherwise)
     int front_bits; // direction-optimizing BFS: pulled rounds read the frontier as bits
     int item_shift; // log2 of the tiles of a frontier work item
     int* rmin;      // CC on a renumbered graph: per-label minimum of the caller's ids,
@@ -235,9 +236,9 @@ hipError_t launch_uf_long(const Round& R, int grid, int block, hipStream_t s);
 // pass: the hooking pass before it (-1: none)
 hipError_t launch_uf_compress(const Round& R, int pass, int grid, int block, hipStream_t s);
 // A whole traversal of a graph of at most kSmallN vertices (or, with R.inst,
-// those of a batch, the largest of max_n vertices and max_m edges) in one launch; a batch
+// those of a batch) in one launch, with the LDS that the largest needs; a batch
 // clears the control block first
-hipError_t launch_small(const Round& R, int algo, int max_n, long long max_m, hipStream_t s);
+hipError_t launch_small(const Round& R, int algo, size_t lds, int grid, hipStream_t s);
 hipError_t launch_small_begin(const Round& R, hipStream_t s);
 // One thread stores v into the pinned host word *p (system scope) once every
 // earlier kernel of the stream has completed.

@@ -156,11 +156,10 @@ struct gg_graph_s {
     double avg_w = 0;  // mean edge weight (0 when unweighted)
     int max_w = 0;     // largest edge weight
     gg_ws_s* ws0 = nullptr;
-    // group of a batch whose instances all fit a workgroup: their vertex
-    // ranges (device, instances + 1) and the largest sizes among them
-    int* inst = nullptr;
-    int inst_max_n = 0;
-    long long inst_max_m = 0;
+    // group of a batch whose instances all fit a workgroup: first vertex, end,
+    // source and edges of each (device), and the most LDS that one needs
+    int4* inst = nullptr;
+    size_t inst_lds = 0;
 };
 
 namespace gg {
