@@ -473,9 +473,10 @@ int gg_graph_class(gg_graph g, int32_t* size_class, int32_t* skew_class, int32_t
  * and graph class (gg_class_of) are concatenated into one graph with
  * per-instance vertex offsets, so every instance is a separate component
  * and one multi-source traversal of the group computes all of them exactly
- * as separate calls would (bit-identical).  Instances small enough for one
- * workgroup each (see gg_stats) form one group per algorithm, one launch for
- * all of them.  Each other group runs in the variant
+ * as separate calls would (bit-identical).  Instances small enough for a
+ * workgroup (see gg_stats) form one group per algorithm, one launch for all
+ * of them, where that is faster: not thousands of tiny ones, few large ones or
+ * large sparse ones, which may be deep.  Each other group runs in the variant
  * the tuner picks for the group's graph (a near-far pick runs as the plain
  * worklist: the buckets pay off on large single-source traversals, not on a
  * group of small ones), on a stream of its own; after the

@@ -72,8 +72,50 @@ bool valid_instance(const gg_instance& x, int* max_deg) {
     return true;
 }
 
-bool fits_workgroup(const gg_instance& x) {
-    return x.n <= kSmallN && x.m <= kSmallM;
+// Whether an instance is traversed by one workgroup.  Above 2^16 edges not where
+// few edges a vertex and no long row make a deep graph likely: a 160 x 160 grid
+// takes one workgroup 3.7 ms, the rounds of all CUs 2.5; an R-MAT or uniform
+// graph of 2^17 edges 0.15-0.23 ms either way, and there the group gains.
+bool fits_workgroup(const gg_instance& x, int max_deg) {
+    int32_t sc = 0, kc = 0, dc = 0;
+    gg_class_of(x.m, x.n, max_deg, -1, &sc, &kc, &dc);
+    return x.n <= kSmallN && x.m <= kSmallM && (x.m <= 65536 || x.m >= 6LL * x.n || kc > 0);
+}
+
+// Whether `count` instances, m edges in all, are one launch, where the longest of
+// those that may hold it up has `longest` (0: none).
+//
+// A CU needs 7-10 us for the smallest, so beyond some number the rounds of all CUs
+// together are faster; in us, rounds / one launch:
+//   edges each        250           1000          4000          8000
+//   SSSP   64      105 /  86      96 / 105      97 / 200     100 / 324
+//        1024      162 /  84     171 / 123     246 / 269     295 / 465
+//        4096      206 /  90     304 / 149     516 / 374     783 / 699
+//   BFS  1024       77 /  81      82 / 103     123 / 201     172 / 340
+//        4096       90 /  84     134 / 115     232 / 242     303 / 443
+// A launch lasts as long as its longest instance, so a few large ones are not
+// (SSSP of uniform graphs takes long either way: 131,072 edges 216-310 / 255):
+//   instances          1             4             8            16
+//   SSSP 80000     108 / 136     118 / 137     138 / 137     270 / 137
+//       131072     128 / 197     148 / 194     288 / 195     426 / 196
+//   BFS  80000      81 /  99      83 / 101      83 / 100     120 / 100
+//       131072      85 / 143      91 / 143      89 / 144     103 / 146
+constexpr long long kFewEdges = 32768;
+
+bool longest_ok(int algo, long long m, long long longest) {
+    return longest <= kFewEdges || m >= (algo == GG_ALGO_SSSP ? 6 : 20) * longest;
+}
+
+bool one_launch(int algo, long long count, long long m, long long longest) {
+    const double each = (double)m / (double)std::max(1LL, count);
+    return longest_ok(algo, m, longest) &&
+           (double)count <= (algo == GG_ALGO_SSSP ? 512 + 2.5 * each : each * each / 4096);
+}
+
+bool holds_up(const gg_instance& x, int max_deg) {
+    int32_t sc = 0, kc = 0, dc = 0;
+    gg_class_of(x.m, x.n, max_deg, -1, &sc, &kc, &dc);
+    return x.algo == GG_ALGO_BFS || kc > 0;
 }
 
 void destroy_group(Group& G) {
@@ -131,28 +173,49 @@ int gg_batch_create(const gg_instance* inst, int32_t count, uint32_t flags, void
     *out = nullptr;
     if (!inst || count < 1) return GG_EINVAL;
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-    // group key: algorithm and graph class (size, skew) of the instance; the
-    // instances that fit a workgroup form one group per algorithm, which runs
-    // as one launch with a workgroup each (unless that group is too large for a
-    // graph, while those of the classes may not be)
-    long long fit_n[2] = {0, 0}, fit_m[2] = {0, 0};
-    for (int i = 0; i < count; ++i)
-        if ((inst[i].algo == GG_ALGO_SSSP || inst[i].algo == GG_ALGO_BFS) &&
-            fits_workgroup(inst[i])) {
-            fit_n[inst[i].algo] += inst[i].n;
-            fit_m[inst[i].algo] += inst[i].m;
+    // group key: algorithm and graph class (size, skew) of the instance.  The
+    // instances that fit a workgroup are one group per algorithm, which runs as
+    // one launch, unless they are too many for that, or too large together for a
+    // graph, while those of a class may not be.  Few large ones stay out of it,
+    // where no larger instance takes as long anyway.
+    std::vector<int> max_deg((size_t)count);
+    std::vector<char> fits((size_t)count), holds((size_t)count);
+    std::vector<long long> large[2];  // edges of those that may hold the launch up
+    long long fit_count[2] = {0, 0}, fit_n[2] = {0, 0}, fit_m[2] = {0, 0};
+    bool all_fit = true;
+    for (int i = 0; i < count; ++i) {
+        if (!valid_instance(inst[i], &max_deg[i])) return GG_EINVAL;
+        fits[i] = fits_workgroup(inst[i], max_deg[i]);
+        holds[i] = holds_up(inst[i], max_deg[i]);
+        all_fit = all_fit && fits[i];
+        if (!fits[i]) continue;
+        const int a = inst[i].algo;
+        fit_count[a]++;
+        fit_n[a] += inst[i].n;
+        fit_m[a] += inst[i].m;
+        if (holds[i]) large[a].push_back(inst[i].m);
+    }
+    bool one[2];
+    long long most[2] = {kSmallM, kSmallM};  // edges of an instance of the one launch
+    for (int a = 0; a < 2; ++a) {
+        long long n = fit_n[a], m = fit_m[a], left = fit_count[a];
+        std::sort(large[a].begin(), large[a].end());
+        while (all_fit && !large[a].empty() && !longest_ok(a, m, large[a].back())) {
+            most[a] = large[a].back() - 1;
+            m -= large[a].back();
+            left--;
+            large[a].pop_back();
         }
+        one[a] = left > 0 && n < (1LL << 31) && fit_m[a] < (1LL << 31) && one_launch(a, left, m, 0);
+    }
     std::map<std::tuple<int, int, int>, std::vector<int>> keys;
     for (int i = 0; i < count; ++i) {
-        int md = 0;
-        if (!valid_instance(inst[i], &md)) return GG_EINVAL;
         int32_t sc = 0, kc = 0, dc = 0;
-        gg_class_of(inst[i].m, inst[i].n, md, -1, &sc, &kc, &dc);
+        gg_class_of(inst[i].m, inst[i].n, max_deg[i], -1, &sc, &kc, &dc);
+        const int a = inst[i].algo;
         if (flags & GG_BATCH_ONE_GROUP) sc = kc = 0;
-        else if (fits_workgroup(inst[i]) && fit_n[inst[i].algo] < (1LL << 31) &&
-                 fit_m[inst[i].algo] < (1LL << 31))
-            sc = kc = -1;
-        keys[std::make_tuple(inst[i].algo, sc, kc)].push_back(i);
+        else if (fits[i] && one[a] && !(holds[i] && inst[i].m > most[a])) sc = kc = -1;
+        keys[std::make_tuple(a, sc, kc)].push_back(i);
     }
     gg_batch b = new (std::nothrow) gg_batch_s();
     if (!b) return GG_ENOMEM;
@@ -212,8 +275,12 @@ int gg_batch_create(const gg_instance* inst, int32_t count, uint32_t flags, void
             hipHostMalloc(reinterpret_cast<void**>(&G.h_ctl), 2 * sizeof(int)) != hipSuccess)
             return bail(GG_EHIP);
         bool fit = true;
-        for (int i : G.members) fit = fit && fits_workgroup(inst[i]);
-        if (fit) {
+        long long longest = 0;
+        for (int i : G.members) {
+            fit = fit && fits[i];
+            if (holds[i] && all_fit) longest = std::max<long long>(longest, inst[i].m);
+        }
+        if (fit && one_launch(G.algo, (long long)G.members.size(), G.m, longest)) {
             // the longest first, so that none of them starts last
             std::vector<int4> first;
             for (size_t k = 0; k < G.members.size(); ++k) {

@@ -1,6 +1,6 @@
 """Batches of instances that one workgroup each could traverse: more than run at
 once, so that a workgroup takes several of different sizes in turn; too many
-tiny ones; a large one among them, first and last.
+tiny ones; a large one among them, first and last; a deep one.
 """
 import time
 
@@ -8,7 +8,8 @@ import numpy as np
 import pytest
 
 import oracle
-from helpers import random_graph
+from helpers import path_graph, random_graph
+from paper_1903_01665_amd import gen
 
 pytestmark = pytest.mark.gpu
 
@@ -53,7 +54,9 @@ def test_many_tiny_instances(algo, count):
     graphs = tiny(90, count)
     inst = [(algo, graphs[i % 90], (i * 7) % graphs[i % 90].n) for i in range(count)]
     print(algo, count, flush=True)
-    run_and_check(inst)
+    groups = run_and_check(inst)
+    if algo == 0:  # one launch up to 512 + 2.5 edges an instance
+        assert (len(groups) == 1) == (count < 1500)
 
 
 @pytest.mark.parametrize("algo", [0, 1])
@@ -62,6 +65,30 @@ def test_a_large_instance_among_tiny_ones(algo):
     rest = [(algo, g, g.n // 2) for g in graphs * 7]
     for at in (0, 100, len(rest)):
         run_and_check(rest[:at] + [(algo, big, 77)] + rest[at:], 2)
+
+
+@pytest.mark.parametrize("algo", [0, 1])
+def test_sparse_instances_above_65536_edges_run_in_rounds(algo):
+    """... as they may be deep; the others, small or with more edges a vertex,
+    are one launch beside them."""
+    grid = gen.grid(160, 160, 0, 8, 1, 1000, stream=5)  # 101,760 edges, no long row
+    graphs = [random_graph(np.random.default_rng(1), 5000, 30000, 1, 9),
+              path_graph(3000, np.ones(2999)), large()]
+    groups = run_and_check([(algo, g, 5) for g in graphs] + [(algo, grid, 0)])
+    assert sorted(g["instances"] for g in groups) == [1, 3]
+    # its rounds are launches: as many as its depth asks for
+    assert [g["captured_rounds"] > 10 for g in groups if g["instances"] == 1] == [True]
+
+
+@pytest.mark.parametrize("algo, few, many", [(0, 4, 8), (1, 16, 24)])
+def test_a_few_large_instances_stay_out_of_the_launch(algo, few, many):
+    """Their rounds are faster than the launch that waits for one of them."""
+    hub = gen.rmat(13, 1 << 17, stream=6)
+    small = [(algo, g, 0) for g in tiny(20, 5)]
+    for count in (few, many):
+        groups = run_and_check(small + [(algo, hub, i) for i in range(count)], 2)
+        assert sorted(g["instances"] for g in groups) == \
+            ([20 + many] if count == many else sorted([20, few]))
 
 
 @pytest.mark.parametrize("algo", [0, 1])
