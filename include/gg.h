@@ -209,13 +209,14 @@ typedef struct {
 #define GG_OPT_LISTS_CHECKED 4u
 #define GG_OPT_LISTS_DIRECT 8u
 
-/* Statistics of the last traversal run on a workspace. */
-/* A small graph (up to 32,768 vertices; up to 65,536 edges, BFS 32,768) whose
+/* Statistics of the last traversal run on a workspace.
+ * A small graph (up to 32,768 vertices; up to 65,536 edges, BFS 32,768) whose
  * call leaves mode, schedule, mapping and time limit to the library, and an
  * instance of a batch of up to 32,768 vertices and 131,072 edges, is traversed
- * by one workgroup in one launch: the variant reported is then the one AUTO
- * resolves to, iterations counts that launch's own rounds, and block_threads
- * is 1024. */
+ * by one workgroup in one launch where that is faster (SSSP and BFS not on
+ * graphs known or likely to be deep): the variant reported is then the one
+ * AUTO resolves to, iterations counts that launch's own rounds, and
+ * block_threads is 1024. */
 typedef struct {
     int32_t algo, mode, sched, mapping; /* the variant that ran (AUTO resolved) */
     int32_t status;                     /* device-side gg_status of that run */

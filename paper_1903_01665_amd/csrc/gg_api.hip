@@ -478,8 +478,8 @@ void resolve(gg_graph g, int algo, const gg_opts* in, gg_opts* out) {
 }
 
 // Whether a call runs as one workgroup: every variant field and the time limit
-// left to the library (a launch cannot be stopped half-way), and a graph below
-// the sizes up to which one workgroup is faster; or a group of a batch made so.
+// left to the library (a launch cannot be stopped half-way), and a graph of the
+// sizes and shapes with which one workgroup is faster; or a group of a batch made so.
 bool whole_ok(gg_graph g, int algo, int nsrc, const gg_opts* in) {
     if (nsrc > 0) return g->inst != nullptr;
     if (in && (in->mode == GG_VERTEX || in->mode == GG_EDGE ||
@@ -487,7 +487,11 @@ bool whole_ok(gg_graph g, int algo, int nsrc, const gg_opts* in) {
                (in->mapping >= GG_MAP_THREAD && in->mapping <= GG_MAP_BALANCED) ||
                in->time_limit_ms > 0))
         return false;
-    return g->n <= kSmallN && g->m <= small_max_edges(algo);
+    if (g->n > kSmallN || g->m > small_max_edges(algo)) return false;
+    if (algo == GG_ALGO_CC) return true;
+    const bool skewed = (double)g->max_deg * g->n >= 128.0 * (double)g->m;
+    return !small_deep(algo, g->m, g->levels) && !(skewed && g->n > kSmallSkewedN) &&
+           (g->levels >= 0 || !small_even(g->n, g->m, g->max_deg));
 }
 
 }  // namespace

@@ -72,14 +72,16 @@ bool valid_instance(const gg_instance& x, int* max_deg) {
     return true;
 }
 
-// Whether an instance is traversed by one workgroup.  Above 2^16 edges not where
-// few edges a vertex and no long row make a deep graph likely: a 160 x 160 grid
+// Whether an instance is traversed by one workgroup.  Not where even degrees
+// (small_even) or, above 2^16 edges, few edges a vertex and no long row make a
+// deep graph likely: a 160 x 160 grid
 // takes one workgroup 3.7 ms, the rounds of all CUs 2.5; an R-MAT or uniform
 // graph of 2^17 edges 0.15-0.23 ms either way, and there the group gains.
 bool fits_workgroup(const gg_instance& x, int max_deg) {
     int32_t sc = 0, kc = 0, dc = 0;
     gg_class_of(x.m, x.n, max_deg, -1, &sc, &kc, &dc);
-    return x.n <= kSmallN && x.m <= kSmallM && (x.m <= 65536 || x.m >= 6LL * x.n || kc > 0);
+    return x.n <= kSmallN && x.m <= kSmallM && (x.m <= 65536 || x.m >= 6LL * x.n || kc > 0) &&
+           !small_even(x.n, x.m, max_deg);
 }
 
 // Whether `count` instances, m edges in all, are one launch, where the longest of

@@ -48,3 +48,48 @@ def test_cc_of_a_chain(order):
             assert min(times) < 0.7
         finally:
             g.free()
+
+
+def grid(w, h):
+    return gen.grid(w, h, 0, 8, 1, 1000, stream=w)
+
+
+def star(n):
+    return gen.from_edges(n, np.zeros(n - 1, np.int32), np.arange(1, n), np.ones(n - 1, np.int32),
+                          name=f"star{n}")
+
+
+def uniform(n, m):
+    return random_graph(np.random.default_rng(n + m), n, m, 1, 100)
+
+
+# (graph, probed, which of SSSP, BFS and CC run as one workgroup)
+RULE = [(uniform(32768, 32768), False, "sbc"), (uniform(32769, 32768), False, ""),
+        (uniform(5000, 32768), True, "sbc"), (uniform(5000, 32769), True, "sc"),
+        (uniform(5000, 65536), False, "sc"), (uniform(5000, 65537), False, ""),
+        (grid(32, 32), True, "sc"), (grid(32, 34), True, "c"), (grid(64, 64), False, "sbc"),
+        (grid(64, 64), True, "c"), (grid(109, 110), False, "sc"), (grid(110, 110), False, "c"),
+        (star(20480), False, "sbc"), (star(20481), True, "c")]
+
+
+@pytest.mark.parametrize("hg, probed, whole", RULE, ids=lambda x: getattr(x, "name", str(x)))
+def test_which_calls_run_as_one_workgroup(hg, probed, whole):
+    from paper_1903_01665_amd import gg
+    g = gg.Graph.from_host(hg)
+    try:
+        if probed:
+            g.probe()
+        s = hg.n // 2
+        want = {"s": oracle.sssp(hg.n, hg.row_ptr, hg.col, hg.w, s),
+                "b": oracle.bfs(hg.n, hg.row_ptr, hg.col, s),
+                "c": oracle.cc(hg.n, hg.row_ptr, hg.col)}
+        calls = {"s": lambda **k: g.sssp(s, **k), "b": lambda **k: g.bfs(s, **k), "c": g.cc}
+        for k, call in calls.items():
+            np.testing.assert_array_equal(call().cpu().numpy(), want[k])
+            assert g.stats()["block_threads"] == (1024 if k in whole else 256), k
+            for o in (dict(mode=gg.EDGE, sched=gg.SYNC), dict(mapping=gg.MAP_BALANCED),
+                      dict(time_limit_ms=60000)):
+                np.testing.assert_array_equal(call(opts=gg.make_opts(**o)).cpu().numpy(), want[k])
+                assert g.stats()["block_threads"] == 256, (k, o)
+    finally:
+        g.free()
