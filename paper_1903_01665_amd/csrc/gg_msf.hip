@@ -61,8 +61,14 @@ constexpr int kMsfSlots = 1024;  // roots whose offers a block collects
 // five edges per vertex one phase is faster (a uniform graph of 2^17 vertices
 // and 2^19 edges 0.60 ms in two phases, 0.53 in one; of 2^21 and 2^24 2.15 and
 // 2.67; R-MAT, sixteen per vertex, the same within 8% from 0.5 to 3 per vertex).
+// Below 2^18 edges as well: each phase's rounds are launches that do little there
+// (us, two phases / one: uniform, eight per vertex, 2^13 edges 280 / 217, 2^17
+// 375 / 343, 2^18 385 / 416, 2^20 565 / 692; R-MAT 2^13 220 / 154, 2^18 282 / 249,
+// 2^20 335 / 289, 2^22 414 / 419; uniform, 32 per vertex, 2^17 312 / 292, 2^18
+// 353 / 395, 2^20 463 / 630).
 constexpr double kLightPerVertex = 1.0;
 constexpr double kLightMost = 0.2;
+constexpr long long kLightLeast = 1 << 18;  // edges
 constexpr int kMsfSample = 8192;  // weights sampled for the light quantile
 constexpr int kMsfBatch = 2;
 
@@ -486,7 +492,7 @@ int gg_msf(gg_graph g, gg_ws ws, uint8_t* in_msf_dev, int64_t* total_weight, int
     M.m = m;
     const double share = m > 0 ? kLightPerVertex * n / m : 1.0;
     M.steps = steps;
-    M.light = share < kLightMost ? std::max(1, (int)(share * kMsfSample)) : 0;
+    M.light = share < kLightMost && m >= kLightLeast ? std::max(1, (int)(share * kMsfSample)) : 0;
     M.max_w = g->max_w;
     M.mask = ws->msf_mask;
     M.parent = ws->msf_parent;
