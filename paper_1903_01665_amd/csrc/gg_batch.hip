@@ -110,7 +110,7 @@ bool longest_ok(int algo, long long m, long long longest) {
 
 bool one_launch(int algo, long long count, long long m, long long longest) {
     const double each = (double)m / (double)std::max(1LL, count);
-    return longest_ok(algo, m, longest) &&
+    return m <= kSmallGroupM && longest_ok(algo, m, longest) &&
            (double)count <= (algo == GG_ALGO_SSSP ? 512 + 2.5 * each : each * each / 4096);
 }
 
@@ -208,7 +208,7 @@ int gg_batch_create(const gg_instance* inst, int32_t count, uint32_t flags, void
             left--;
             large[a].pop_back();
         }
-        one[a] = left > 0 && n < (1LL << 31) && fit_m[a] < (1LL << 31) && one_launch(a, left, m, 0);
+        one[a] = left > 0 && n < (1LL << 31) && one_launch(a, left, m, 0);
     }
     std::map<std::tuple<int, int, int>, std::vector<int>> keys;
     for (int i = 0; i < count; ++i) {

@@ -100,6 +100,10 @@ inline bool small_even(long long n, long long m, long long max_deg) {
     return n > kSmallEvenN && m >= 2 * n && max_deg * n <= 2 * m;
 }
 constexpr int kSmallBlock = 1024;
+// Edges of a batch's group up to which no edge number of a whole traversal passes
+// the int range: a sweep counts in steps of four edges a thread, and looks a step
+// ahead of one that may begin as far past the last edge.
+constexpr long long kSmallGroupM = (1LL << 31) - 1 - 3 * 4 * kSmallBlock;
 // Bytes of LDS: 4 per vertex, 2 bits of frontier, and SSSP and BFS 4 per chunk
 // of a long row (rows of more than 64 edges in chunks of 256).
 inline size_t small_lds(int algo, int n, long long m) {

@@ -1993,7 +1993,7 @@ __device__ __forceinline__ void small_chunk(const Round& R, int base, int* dist,
 // A dense round: every edge of the instance whose tail is reached (SSSP) or on
 // the level (BFS) is relaxed, four edges per 16-byte load, with no search for
 // rows and every lane busy; the next step's edges load while this one's are
-// relaxed.
+// relaxed.  (Edge numbers go up to two steps past the last edge: kSmallGroupM.)
 struct SmallEdges {
     int u[4], t[4];
     unsigned w[4];
@@ -2572,13 +2572,13 @@ __global__ __launch_bounds__(256) void k_uf(Round R) {
     Acc acc;
     if (R.r == 0) {
         for (long long v = tid; v < g.n; v += tt) {
-            const int b = g.srow[v], e1 = min(b + kUfFirst, g.srow[v + 1]);
+            const int b = g.srow[v], deg = min(kUfFirst, g.srow[v + 1] - b);
             int x[kUfFirst], least = (int)v;
 #pragma unroll
-            for (int k = 0; k < kUfFirst; ++k) x[k] = b + k < e1 ? g.scol[b + k] : (int)v;
+            for (int k = 0; k < kUfFirst; ++k) x[k] = k < deg ? g.scol[b + k] : (int)v;
 #pragma unroll
             for (int k = 0; k < kUfFirst; ++k) least = min(least, x[k]);
-            acc.e += e1 - b;
+            acc.e += deg;
             if (least < v) {
                 parent[v] = least;
                 acc.u++;
@@ -2698,10 +2698,10 @@ __global__ __launch_bounds__(256) void k_uf_hook(Round R, int pass, int share, i
     for (long long v = tid * step + first; v < g.n; v += tt * step) {
         const int r = parent[v];
         if (ROOTS && r != v) continue;
-        const int b = g.srow[v], e1 = min(b + K, g.srow[v + 1]);
+        const int b = g.srow[v], deg = g.srow[v + 1] - b;
         int x[K], least = r;
 #pragma unroll
-        for (int k = 0; k < K; ++k) x[k] = b + k < e1 ? g.scol[b + k] : (int)v;
+        for (int k = 0; k < K; ++k) x[k] = k < deg ? g.scol[b + k] : (int)v;
 #pragma unroll
         for (int k = 0; k < K; ++k) x[k] = parent[x[k]];
 #pragma unroll

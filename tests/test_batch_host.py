@@ -29,3 +29,15 @@ got = create({shapes})
 print(got)
 assert got == {rc}
 """, tmp_path)
+
+
+def test_edge_numbers_of_the_one_launch_stay_in_range(tmp_path):
+    """2^31 - 8192 edges are a graph, but the launch counts past its last edge: the
+    two classes stay apart.  (Together they are 8 GB of columns, for which the process
+    has no room; the small class comes first and finds no device memory.)"""
+    run("import resource\nresource.setrlimit(resource.RLIMIT_AS, (6 << 30, 6 << 30))\n" + BATCH +
+        """
+got = create([131072] * 16383 + [32768] * 3 + [24576])
+print(got)
+assert got == -2
+""", tmp_path)
