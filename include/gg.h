@@ -34,7 +34,7 @@
  *     only the device can tell when it has ended, so the plain calls
  *     (gg_sssp, gg_bfs, gg_cc and their _ex forms) keep the calling host
  *     thread until the device has reported the end: the output values are
- *     then final, while up to one batch of rounds past the end (which
+ *     then final, while up to four rounds past the end (which
  *     return at their first instruction) may still be queued on `stream`;
  *     work enqueued on `stream` afterwards runs after them.  The _async
  *     forms (gg_sssp_async and below) return at once with a ticket; one host
@@ -328,9 +328,8 @@ int gg_cc_ex(gg_graph g, gg_ws ws, const gg_opts* opts, int32_t* label_out_dev, 
  * rounds run on one of eight streams of the library (taken in turn; the
  * first call makes them), after the work the caller enqueued on `stream`
  * before the call and after the workspace's previous traversal; the driver
- * thread launches the next
- * batch of rounds of every traversal in flight as soon as the previous one
- * completes.  Same arguments, results and errors as the _ex forms, plus:
+ * thread keeps a few rounds of every traversal in flight enqueued ahead of
+ * the one the device is in.  Same arguments, results and errors as the _ex forms, plus:
  *   ticket  (host, out) the handle of the traversal, freed by gg_ticket_free.
  * The workspace (ws NULL = the graph's default one) stays taken until the
  * traversal ends: any call on it meanwhile, gg_last_stats and gg_ws_free
@@ -537,9 +536,9 @@ int gg_batch_free(gg_batch b);
  * slot is free and the per-query state of all admitted queries (a
  * workspace: frontier flags and heavy-row bits, ~2.3 bytes per vertex) fits the
  * memory budget, enqueues each admitted query's rounds on the slot's own
- * stream, and launches a query's next batch of rounds as soon as its
- * previous one completes, so the kernels of different queries overlap on
- * the device.  A query's result is bit-identical to the same call made
+ * stream, and keeps a few of a query's rounds enqueued ahead of the one
+ * the device is in, so the kernels of different queries overlap on the
+ * device.  A query's result is bit-identical to the same call made
  * alone.  Every call may come from any thread. */
 typedef struct gg_server_s* gg_server;
 

@@ -771,7 +771,7 @@ long long max_rounds(const Plan& p) {
 }
 
 // Eager driver as a resumable state machine.  Every round kernel tells the host
-// that its round is running, and the host keeps a few rounds enqueued beyond it
+// as it ends which round is next, and the host keeps a few rounds enqueued beyond it
 // (kAhead, kAheadPolled) until a round kernel reports the end by storing the
 // traversal's tag into the pinned word.  Rounds enqueued past the end return at
 // their first instruction.  A whole traversal is one launch, whose completion

@@ -10,10 +10,9 @@
 // The rounds run on one of a few streams of the library, taken in turn,
 // ordered after everything the caller enqueued on its stream before the call
 // (an event recorded there) and after the workspace's previous traversal.
-// The driver thread keeps two batches of rounds in flight per traversal and
-// reads their completion from pinned host words written by marker kernels
-// (no runtime call while it polls), launching the next batch of each
-// traversal as soon as the previous one has completed.  The caller's stream
+// The driver thread keeps a few rounds of each traversal enqueued ahead of the
+// one the device is in, which the round kernels report in pinned host words (no
+// runtime call while it polls).  The caller's stream
 // is never made to wait on work that is not yet enqueued: a stream blocked
 // that way could share a hardware queue with the rounds it waits for.
 
@@ -93,8 +92,8 @@ void finish_traversal(gg_ticket t, int rc) {
 }
 
 // The driver: sleeps while nothing is in flight; otherwise takes over the
-// traversals callers handed in and advances every traversal it holds by at
-// most one batch per pass, yielding between passes that change nothing.  The
+// traversals callers handed in and enqueues what each may have enqueued, once
+// per pass, yielding between passes that change nothing.  The
 // lock is held only to take new traversals and to mark ended ones: polling
 // and launching happen outside it, so a caller handing in a traversal never
 // waits behind the driver's work.

@@ -24,11 +24,15 @@ constexpr int kItemTiles = 8;        // most tiles of a frontier work item
 constexpr int kFillWaves = 8192;     // wavefronts that fill the device (256 CUs x 32)
 // Hooking passes of CC by union-find and, for all but the first, the share of
 // the vertices they look from: by the neighbours a vertex has (ms / n, both
-// directions).  Trees of a sparse graph touch in few places: with 2 neighbours
-// a vertex (2^18 vertices) three passes leave enough apart that linking the
-// rest takes 1.30 ms, with five passes all of CC takes 0.13; with 4 neighbours
-// (2^22 vertices) three take 0.75, five 1.15 ms; with 8 three passes from one
-// vertex in eight do (2^20 vertices: 0.19 ms).
+// directions).  Trees of a sparse graph touch in few places, so three passes leave
+// many apart for the last phase; with more neighbours they join most.  All of CC,
+// us, uniform graphs, three passes / five:
+//   neighbours      1           1.5          2           2.8         4           7.8
+//   2^18       152 / 161   399 / 151    380 / 152   175 / 150   134 / 150   138 / 150
+//   2^20       194 / 225   541 / 241   1268 / 259   233 / 259   223 / 266   228 / 264
+//   2^22       487 / 649   737 / 757   1442 / 865  1093 / 986   761 / 1129  819 / 1080
+// With 8 neighbours and more it is enough to look from one vertex in eight after
+// the first pass (16 neighbours, 2^22 vertices: 521 us, from all of them 915).
 struct UfPlan {
     int passes, share;
 };
@@ -51,13 +55,15 @@ inline int item_shift_for(long long ntiles) {
 }
 
 // Edges per heavy-row chunk: the least power of two from 128 that cuts the
-// graph into at most four chunks for each of kFillWaves wavefronts (512 from
-// 2^25 edges on, the best size measured there).  With 512-edge chunks and 64
-// chunks a wavefront the dense chunk rounds of an R-MAT graph of 2^22 edges
-// took 148 and 97 us (132 blocks); with 128-edge chunks, four a wavefront, 84
-// and 73 us: what is left there is the rate of its atomics (27 G/s at most on
-// this device, about 8 G/s on skewed heads, whatever the scope; plain loads
-// and stores run at 60-400 G/s).
+// graph into at most four chunks for each of kFillWaves wavefronts: 256 above 2^22
+// edges, 512 above 2^23.  With 512-edge chunks and 64 chunks a wavefront the dense
+// chunk rounds of an R-MAT graph of 2^22 edges took 148 and 97 us (132 blocks); with
+// 128-edge chunks, four a wavefront, 84 and 73 us: what is left there is the rate of
+// its atomics (27 G/s at most on this device, about 8 G/s on skewed heads, whatever
+// the scope; plain loads and stores run at 60-400 G/s).  On larger graphs the size
+// matters less, and the list of chunks is shorter with long ones (8 bytes each).  R-MAT,
+// us with 128, 256 and 512: SSSP 2^24 edges 608, 636, 645, 2^26 1568, 1574, 1605; BFS
+// 2^24 232, 230, 225, 2^26 505, 493, 499.
 inline int chunk_for(long long m) {
     int c = 128;
     while (c < kChunk && m / c > 4 * kFillWaves) c *= 2;
@@ -154,6 +160,18 @@ struct Stat {
     long long edges, verts, updates, pushes;
     long long swept;  // edges read by the sweeps of a per-round CC schedule
 };
+
+// Waits for the loads of x here.  Loads under a lane mask are followed by a
+// join where the compiler no longer knows how many are in flight, so each
+// later use inside a branch of its own waits for everything outstanding --
+// also the gathers, stores and atomics of the branches before it, which then
+// run one after another (4096 x 4096 grid, SSSP: 19.95 ms so, 18.96 with the
+// waits here; worklist on an R-MAT graph of 2^18 vertices 464 and 432 us).
+template <int U>
+__device__ __forceinline__ void landed(int (&x)[U]) {
+#pragma unroll
+    for (int j = 0; j < U; ++j) asm volatile("" : "+v"(x[j]));
+}
 
 // Device view of an uploaded graph.  Arrays are owned by the host-side
 // handle.  The CSR keeps the input's row order; src is the edge-list form.

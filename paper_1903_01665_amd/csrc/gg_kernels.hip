@@ -265,18 +265,6 @@ __device__ __forceinline__ void wave_rows_balanced(int beg, int deg, int sv, F&&
 
 // ---------------------------------------------------------- algorithms ----
 
-// Waits for the loads of x here.  Loads under a lane mask are followed by a
-// join where the compiler no longer knows how many are in flight, so each
-// later use inside a branch of its own waits for everything outstanding --
-// also the gathers, stores and atomics of the branches before it, which then
-// run one after another (4096 x 4096 grid, SSSP: 19.95 ms so, 18.96 with the
-// waits here; worklist on an R-MAT graph of 2^18 vertices 464 and 432 us).
-template <int U>
-__device__ __forceinline__ void landed(int (&x)[U]) {
-#pragma unroll
-    for (int j = 0; j < U; ++j) asm volatile("" : "+v"(x[j]));
-}
-
 // Relax one edge e (p -> t = col[e]) with the tail's value sv.  Returns true
 // when this lane lowered val[t] (the caller pushes t or counts an update).
 template <int A>
@@ -2101,7 +2089,7 @@ __global__ __launch_bounds__(kSmallBlock) void k_small(Round R) {
         int* dist = s_mem;
         unsigned* fb = reinterpret_cast<unsigned*>(s_mem + n);
         const int e_begin = g.row[base], e_end = g.row[base + n];
-        unsigned* queue = fb + 2 * words;  // small_queue(most edges of an instance) entries
+        unsigned* queue = fb + 2 * words;  // chunks of long rows (small_lds bounds them)
         for (int v = threadIdx.x; v < n; v += kSmallBlock) dist[v] = v == source ? 0 : kInf;
         for (int k = threadIdx.x; k < 2 * words; k += kSmallBlock)
             fb[k] = k == (source >> 5) ? 1u << (source & 31) : 0;

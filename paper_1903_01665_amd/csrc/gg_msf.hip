@@ -229,19 +229,15 @@ __device__ __forceinline__ void offer_to(const Msf& M, const Offers& o, int root
     }
 }
 
-// Waits for the loads of x here: after loads under a lane mask every later use
-// in a branch of its own would wait for everything outstanding.  With the
-// parents of a lane's four edges in flight together the forest of an R-MAT graph
-// of 2^20 vertices takes 774 us, edge by edge 810.  (The roots' offers together
-// too: 745, but 96 registers, and a uniform graph of 2^17 vertices 640 for 550.)
-template <int U>
-__device__ __forceinline__ void landed(int (&x)[U]) {
-#pragma unroll
-    for (int j = 0; j < U; ++j) asm volatile("" : "+v"(x[j]));
-}
-
 // A wavefront takes M.steps * 256 consecutive edges, four per lane at a time;
-// bit `lane` of mask word 4 * (256-edge step) + j stands for a lane's j-th edge.
+// bit `lane` of mask word 4 * (256-edge step) + j stands for a lane's j-th edge.  The
+// parents of a lane's four edges load together (see landed): the forest of an R-MAT
+// graph of 2^20 vertices takes 774 us so, edge by edge 810.  Seven wavefronts a
+// SIMD leave 72 registers, and 6 of a lane's spill (28 bytes of scratch): with six
+// or five and no scratch the same forests take within 4% of this, the uniform one
+// of 2^20 vertices and 5.1 edges a vertex 9% more with five.  (The roots' offers
+// together too: 96 registers, 745 us, but a uniform graph of 2^17 vertices 640 for
+// 550.)
 __global__ __launch_bounds__(256, 7) void k_msf_min(Msf M) {
     bool light, first;
     if (!msf_begin(M, light, first)) return;

@@ -81,8 +81,8 @@ struct gg_ws_s {
     unsigned char* vflag_mem = nullptr;
     int epoch = 0;  // round stamps of the next traversal start here
     // pinned host words: [0] the tag written by the kernel that finds the
-    // end; [2..3] (64 bits) the sequence number of the last batch of rounds
-    // completed, written by a marker kernel (non-blocking driving); [4..5] the
+    // end; [2..3] (64 bits) the sequence number of the last marker kernel that
+    // ran (non-blocking driving: the end of a traversal's launches); [4..5] the
     // rounds reached, written by the round kernels
     int* h_done = nullptr;
     unsigned long long prog_seq = 0;  // last sequence number enqueued
@@ -110,7 +110,7 @@ struct gg_ws_s {
     int small_blocks = 0;  // blocks of the last whole traversal (0: it ran in rounds)
 };
 
-// The 64-bit batch sequence word inside a workspace's pinned block.
+// The 64-bit marker word inside a workspace's pinned block.
 inline unsigned long long* prog_word(gg_ws ws) {
     return reinterpret_cast<unsigned long long*>(ws->h_done + 2);
 }
@@ -252,7 +252,7 @@ long long max_rounds(const Plan& p);
 // Enqueue the first rounds, from round r0.
 int drive_start(Drive& d, long long r0, int stamp_base, int tag);
 // Advance: 1 = finished (d.status holds GG_OK, GG_EITER or GG_ETIMEOUT),
-// 0 = still running (non-blocking form only), < 0 = HIP failure.
+// 0 = still running, < 0 = HIP failure.
 int drive_step(Drive& d);
 // Blocking form: rounds from r0 until the end is reported.
 int plan_drive(Plan& p, long long r0, int stamp_base, int tag, long long* r_end);

@@ -7,10 +7,10 @@
 // by the memory budget.  Admission is first-come first-served: when the
 // head of the queue does not fit (no slot, or its state would exceed the
 // budget), later queries wait behind it.  A driver thread of the server
-// admits queries and advances each one in flight by a batch of rounds as
-// soon as its previous batch completes (non-blocking event queries), so the
-// kernels of different queries overlap on the device and no caller thread
-// sits on the path between two batches; gg_server_poll only hands out the
+// admits queries and keeps a few rounds of each one in flight enqueued ahead of
+// the one the device is in (read from pinned words, without a runtime call), so
+// the kernels of different queries overlap on the device and no caller thread
+// sits on the path between two rounds; gg_server_poll only hands out the
 // finished queries.
 
 #include <algorithm>
@@ -189,7 +189,7 @@ int admit(gg_server s, Query* q, SGraph& G) {
 
 // One pass of the driver with the lock held: admission (first come, first
 // served, while a slot and the memory budget allow), then every query in
-// flight advances by at most one batch.  Returns whether anything changed.
+// flight enqueues the rounds it may.  Returns whether anything changed.
 bool step_locked(gg_server s) {
     bool moved = false;
     while (!s->queue.empty() && (int)s->active.size() < s->slots) {
@@ -250,9 +250,8 @@ bool step_locked(gg_server s) {
 }
 
 // The driver: sleeps while there is nothing to do; otherwise steps, and
-// between steps that change nothing releases the lock and yields (a batch
-// of rounds takes microseconds to milliseconds; polling keeps the gap
-// between a batch's end and the next launch short).
+// between steps that change nothing releases the lock and yields (a round
+// takes microseconds to milliseconds; polling keeps rounds enqueued ahead).
 void drive_loop(gg_server s) {
     (void)hipSetDevice(s->device);
     std::unique_lock<std::mutex> lk(s->mu);
