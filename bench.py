@@ -74,20 +74,24 @@ def log(*a):
 #   CC diropt     swept edges as edge sync (16 B), the other edges, vertices
 #                 and tiles as vertex async; 4 B per update; per push 2 B of
 #                 flags and 8 B for the pushed vertex's row length
-#   CC union-find 8 B per vertex per phase (row offsets), 16 B per linked edge
-#                 (column, two roots, the swap); the compressions as aux
+#   CC union-find 8 B per vertex (its row offset in the first phase, its parent in
+#                 the last: most are in the giant tree and stop there), 4 B per
+#                 edge looked at, 4 B per parent stored
 # heavy kernels: per edge 12 / 8 B, per push 2 B (10 B under CC diropt)
 # aux kernels:   init 4 B per vertex (+2 B of flags when async); CC shortcut
-#                8 B per vertex per launch
+#                8 B per vertex per launch; CC union-find 8 B per vertex for the
+#                first and the last compression (the passes between return at once
+#                when nothing was hooked); the bits of a pulled BFS level are not
+#                counted, as how many levels pulled is not reported
 def algorithmic_bytes(algo, mode, sched, kind, n, prof_kind, launches):
     E = prof_kind["edges_processed"]
     V = prof_kind["vertices_processed"]
     U = prof_kind["updates"]
     P = prof_kind["pushes"]
     if sched == 5 and kind == "round":
-        # union-find: the row offsets of every vertex in the first and the
-        # last phase, the column of every edge looked at, the parents stored
-        return 8 * n * min(launches, 2) + 4 * E + 4 * U
+        return 8 * n + 4 * E + 4 * U
+    if sched == 5 and kind == "aux":
+        return 4 * n + 8 * n * min(2, max(0, launches - 1))
     per_edge = 12 if algo == "sssp" else 8
     if sched == 4 and (algo == "sssp" or (algo == "cc" and mode == 0)):
         # per-round push/pull (SSSP; CC in vertex mode): an edge is 12 B
@@ -118,8 +122,8 @@ def algorithmic_bytes(algo, mode, sched, kind, n, prof_kind, launches):
         return ntiles * launches + 16 * V + per_edge * E + extra + 2 * P
     if kind == "heavy":
         return per_edge * E + 2 * P
-    if algo == "bfs" and sched == 4:  # the bits of a level: 4 B and a bit per vertex
-        return 4 * n + (4 * n + n // 8) * max(0, launches - 1)
+    if algo == "bfs" and sched == 4:
+        return 6 * n
     return (4 + (2 if sched == 1 else 0)) * n + 8 * n * max(0, launches - 1)
 
 
