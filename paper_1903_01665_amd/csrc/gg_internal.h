@@ -90,17 +90,17 @@ inline long long small_max_edges(int algo) { return algo == 1 ? 32768 : 65536; }
 //   probed, levels:    64 x 64 grid, 126        512 / 376    126 x 126, 250  1914 / 766
 //                      16 x 1000 grid, 1015   12936 / 3149   path of 4000    8110 / 8063
 //                      uniform, 16,384 vertices, 32,768 edges, 21             138 / 181
-//                      32 x 32 grid, 62         176 / 218    (up to 4096 edges still)
+//                      35 x 32 grid            137 / 147    4 x 500, 502        1919 / 1320
 //   not probed, even degrees:  110 x 110 grid  1448 / 1427   126 x 126       1911 / 1658
 //                      16 x 1000 grid         12937 / 7749   90 x 90          910 / 1208
 //                      (random graphs of 2 and 4 edges a vertex 138 / 295, 151 / 198)
 //   skewed:            star of 16,384            51 / 55     of 32,768         72 / 57
 constexpr int kSmallLevels = 32;
-constexpr long long kSmallDeepM = 4096;
+constexpr long long kSmallDeepM = 6144;
 constexpr int kSmallEvenN = 12000;
 constexpr int kSmallSkewedN = 20480;
 inline bool small_deep(int algo, long long m, int levels) {
-    return levels > kSmallLevels && !(algo == 0 && m <= kSmallDeepM);
+    return levels > kSmallLevels && !(algo == 0 && levels < 256 && m <= kSmallDeepM);
 }
 inline bool small_even(long long n, long long m, long long max_deg) {
     return n > kSmallEvenN && m >= 2 * n && max_deg * n <= 2 * m;
