@@ -72,11 +72,10 @@ bool valid_instance(const gg_instance& x, int* max_deg) {
     return true;
 }
 
-// Whether an instance is traversed by one workgroup.  Not where even degrees
+// Whether an instance may be traversed by one workgroup.  Not where even degrees
 // (small_even) or, above 2^16 edges, few edges a vertex and no long row make a
-// deep graph likely: a 160 x 160 grid
-// takes one workgroup 3.7 ms, the rounds of all CUs 2.5; an R-MAT or uniform
-// graph of 2^17 edges 0.15-0.23 ms either way, and there the group gains.
+// deep graph likely: a 160 x 160 grid takes one workgroup 3.7 ms, the rounds of
+// all CUs 2.5.
 bool fits_workgroup(const gg_instance& x, int max_deg) {
     int32_t sc = 0, kc = 0, dc = 0;
     gg_class_of(x.m, x.n, max_deg, -1, &sc, &kc, &dc);
