@@ -41,7 +41,8 @@ inline UfPlan uf_plan(long long n, long long ms) {
     return UfPlan{ms >= 3 * n ? 3 : 5, 1};
 }
 constexpr int kUfLong = 7;
-constexpr int kUfSteps = 16;         // steps of a compression's walks but in the last
+constexpr int kUfSteps = 8;          // steps of a compression's walks but in the last
+constexpr int kSmallSteps = 16;      // ... and of a walk in LDS between two barriers
 constexpr int kXcd = 8;              // accelerator dies; workgroups go to them round-robin
 // Tiles per frontier work item, as a shift: the most (up to kItemTiles) that
 // still leave an item for each of kFillWaves wavefronts.  Graphs of 4M

@@ -2152,7 +2152,7 @@ __global__ __launch_bounds__(kSmallBlock) void k_small(Round R) {
 
 // CC through the union-find Set in LDS: every stored edge links its ends, the
 // larger root under the smaller, then every vertex climbs to its root.  A walk
-// stops after kUfSteps steps (unrolled: a counter costs 20%): an edge whose ends
+// stops after kSmallSteps steps (unrolled: a counter costs 20%): an edge whose ends
 // are further from their roots waits until all have climbed, and the edges are
 // gone through again (a path of 32,768 vertices in order, whose links make one
 // chain: 1.35 ms with walks to the end, 0.2 so; few other graphs need it).
@@ -2166,7 +2166,7 @@ __global__ __launch_bounds__(kSmallBlock) void k_small_cc(Round R) {
     auto find = [&](int x) {
         int p = parent[x];
 #pragma unroll
-        for (int k = 0; k < kUfSteps; ++k) {
+        for (int k = 0; k < kSmallSteps; ++k) {
             if (p == x) return x;
             const int gp = parent[p];
             if (gp != p) parent[x] = gp;  // path halving: only non-roots change
@@ -2221,7 +2221,7 @@ __global__ __launch_bounds__(kSmallBlock) void k_small_cc(Round R) {
                     const int v = v0 + j * kSmallBlock;
                     if (v >= g.n) continue;
                     if (x[j] != p[j]) {
-                        for (int k = 0; x[j] != p[j] && k < kUfSteps; ++k) {
+                        for (int k = 0; x[j] != p[j] && k < kSmallSteps; ++k) {
                             p[j] = x[j];
                             x[j] = parent[p[j]];
                         }
@@ -2707,9 +2707,14 @@ __global__ __launch_bounds__(256) void k_uf_hook(Round R, int pass, int share, i
 // path: one in all), whose walks are short only if the vertices above have been
 // hung higher by then, which the dies' caches do not show within a launch.  The
 // chains that a pass leaves are 1/kUfSteps as long or less, and the next
-// compression runs for them.  A path of 2^21 vertices: walks to the end 2.34 ms,
-// of 16 steps 0.19, of 32 0.22; the grid 0.70 (0.58 with three passes before them
-// that hang every vertex two parents higher), 0.48 and 0.53.
+// compression runs for them.  All of CC, ms:
+//   steps                            to the end     32      16       8       4
+//   path of 2^21 vertices                2.34      0.22    0.19    0.18    0.18
+//   4096 x 4096 grid                     0.70      0.53    0.48    0.45    0.46
+//   ... with shortcuts (1%)              2.00      0.99    0.78    0.63    0.55
+//   1024 x 1024 grid                     0.130     0.133   0.126   0.119   0.127
+// (with three passes before them that hang every vertex two parents higher, as on
+// graphs known to be deep before: the grids 0.58, 0.65 and 0.131).
 // LAST: each thread writes its own vertex only (a halving store can land after
 // the owner's own and leave an ancestor that is not the root).
 template <bool LAST>
