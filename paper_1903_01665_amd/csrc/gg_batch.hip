@@ -101,7 +101,9 @@ bool fits_workgroup(const gg_instance& x, int max_deg) {
 //       131072     128 / 197     148 / 194     288 / 195     426 / 196
 //   BFS  80000      81 /  99      83 / 101      83 / 100     120 / 100
 //       131072      85 / 143      91 / 143      89 / 144     103 / 146
-constexpr long long kFewEdges = 32768;
+// (They cost the batch a launch of their own beside it, so up to 2^16 edges they
+// stay: 24 instances of scales 10 and 11, 125 us together, 134 apart.)
+constexpr long long kFewEdges = 65536;
 
 bool longest_ok(int algo, long long m, long long longest) {
     return longest <= kFewEdges || m >= (algo == GG_ALGO_SSSP ? 6 : 20) * longest;
