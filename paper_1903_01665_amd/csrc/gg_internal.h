@@ -87,21 +87,26 @@ constexpr long long kSmallM = 131072;
 inline long long small_max_edges(int algo) { return algo == 1 ? 32768 : 65536; }
 // ... and where the table does not tell: SSSP and BFS only where the graph is not
 // known or likely to be deep, nor skewed and so wide that one CU takes longer than
-// the few rounds (SSSP, us, one CU / a launch per round):
-//   probed, levels:    64 x 64 grid, 126        512 / 376    126 x 126, 250  1914 / 766
-//                      16 x 1000 grid, 1015   12936 / 3149   path of 4000    8110 / 8063
-//                      uniform, 16,384 vertices, 32,768 edges, 21             138 / 181
-//                      35 x 32 grid            137 / 147    4 x 500, 502        1919 / 1320
+// the few rounds.  us, one CU / a launch per round:
+//   probed (grids, sc: with shortcuts)    edges   levels       SSSP          BFS
+//     32 x 32 sc                           4002       31     95 /  152    87 / 109
+//     40 x 40                              6240       77    207 /  223   186 / 166
+//     64 x 32 sc                           8076       49    146 /  199   119 / 121
+//     56 x 56 sc                          12432       47    237 /  242   178 / 153
+//     64 x 64                             16128      125    353 /  321   286 / 237
+//     126 x 126 sc                        63578      100    919 /  397
+//     4 x 500                              6992      502   1919 / 1320  1136 / 963
+//     uniform, 8000 vertices              16000       18    107 /  159    98 / 104
+//     uniform, 16384 vertices             32768       21    152 /  167   131 / 104
+//     uniform, 30000 vertices             40000       41    285 /  240
 //   not probed, even degrees:  110 x 110 grid  1448 / 1427   126 x 126       1911 / 1658
 //                      16 x 1000 grid         12937 / 7749   90 x 90          910 / 1208
 //                      (random graphs of 2 and 4 edges a vertex 138 / 295, 151 / 198)
 //   skewed:            star of 16,384            51 / 55     of 32,768         72 / 57
-constexpr int kSmallLevels = 32;
-constexpr long long kSmallDeepM = 6144;
 constexpr int kSmallEvenN = 12000;
 constexpr int kSmallSkewedN = 20480;
 inline bool small_deep(int algo, long long m, int levels) {
-    return levels > kSmallLevels && !(algo == 0 && levels < 256 && m <= kSmallDeepM);
+    return levels > (algo == 1 ? 20 : 32) && (levels >= 256 || m > (algo == 1 ? 6144 : 12288));
 }
 inline bool small_even(long long n, long long m, long long max_deg) {
     return n > kSmallEvenN && m >= 2 * n && max_deg * n <= 2 * m;
@@ -270,8 +275,8 @@ hipError_t launch_front_bits(const Round& R, int grid, int block, hipStream_t s)
 hipError_t launch_jump(const Round& R, int grid, int block, hipStream_t s);
 hipError_t launch_cc_diropt(const Round& R, int grid, int block, hipStream_t s);
 hipError_t launch_sssp_diropt(const Round& R, int grid, int block, hipStream_t s);
-// CC by union-find (GG_UNIONFIND), round R.r: join, nothing, find the giant
-// root, link the rest; the hooking passes of round 1; the long rows of
+// CC by union-find (GG_UNIONFIND), round R.r: join, hook the roots, find the giant
+// root, link the rest; the later hooking passes of round 1; the long rows of
 // round 3 (graphs with heavy-row chunks); and the compression after each
 hipError_t launch_uf(const Round& R, int grid, int block, hipStream_t s);
 hipError_t launch_uf_hook(const Round& R, int pass, int share, int grid, int block,

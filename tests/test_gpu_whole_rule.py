@@ -67,7 +67,9 @@ def uniform(n, m):
 RULE = [(uniform(32768, 32768), False, "sbc"), (uniform(32769, 32768), False, ""),
         (uniform(5000, 32768), True, "sbc"), (uniform(5000, 32769), True, "sc"),
         (uniform(5000, 65536), False, "sc"), (uniform(5000, 65537), False, ""),
-        (grid(39, 40), True, "sc"), (grid(40, 40), True, "c"), (grid(64, 64), False, "sbc"),
+        (grid(39, 40), True, "sbc"), (grid(40, 40), True, "sc"), (grid(55, 56), True, "sc"),
+        (grid(56, 56), True, "c"), (grid(4, 200), True, "sbc"), (grid(4, 300), True, "c"),
+        (grid(64, 64), False, "sbc"),
         (grid(64, 64), True, "c"), (grid(109, 110), False, "sc"), (grid(110, 110), False, "c"),
         (star(20480), False, "sbc"), (star(20481), True, "c")]
 
