@@ -706,8 +706,10 @@ hipError_t plan_round(Plan& p, int r) {
     };
     const UfPlan uf = uf_plan(p.g->n, p.g->ms);
     for (int k = 0; p.uf && r == 1 && k < uf.passes && e == hipSuccess; ++k) {
-        e = plan_launch(p, KIND_AUX,
-                        [&] { return launch_uf_hook(R, k, uf.share, p.g_round, kBlock, p.s); });
+        if (k > 0)  // the first is the round kernel's
+            e = plan_launch(p, KIND_AUX, [&] {
+                return launch_uf_hook(R, k, uf.share, p.g_round, kBlock, p.s);
+            });
         if (e == hipSuccess) e = compress(k);
     }
     if (e == hipSuccess && p.uf && r == 3 && p.g->n_shchunks > 0)

@@ -2492,8 +2492,8 @@ __global__ __launch_bounds__(256) void k_t_fill(const int* col, const int* w, co
 // Bound by dependent gathers of parents.  Linking every vertex with its first
 // two neighbours by compare-and-swap built deep trees under contention: 7.4 ms
 // on a uniform graph of 2^23 vertices and 2^26 edges, where edge sweeps take
-// 2.5 ms; linking only round 0's roots 2.4 ms; now 0.93 ms (R-MAT, 2^22
-// vertices and 2^26 edges: 0.30 -> 0.23 ms).
+// 2.5 ms; linking only round 0's roots 2.4 ms; now 0.95 ms (R-MAT, 2^22
+// vertices and 2^26 edges: 0.30 -> 0.25 ms).
 constexpr int kUfFirst = 8;
 
 __device__ __forceinline__ int uf_load(int* p, int x) {
@@ -2551,6 +2551,36 @@ __device__ __forceinline__ void uf_link_batch(int* parent, const int* col, int l
         if (x[j] != pv) acc.u += uf_link(parent, pv, x[j]);
 }
 
+// A hooking pass of round 1: of every vertex (ROOTS: every root), or of one in
+// `step` from `first` on, the root takes the smallest parent that the vertex's
+// first neighbours have.  Returns whether this lane hooked anything.
+template <bool ROOTS>
+__device__ __forceinline__ bool uf_hook(const Round& R, int step, int first) {
+    const DevGraph& g = R.g;
+    bool hooked = false;
+    int* parent = R.val;
+    constexpr int K = ROOTS ? kUfFirst : kUfFirst / 2;
+    const long long tid = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    const long long tt = (long long)gridDim.x * blockDim.x;
+    for (long long v = tid * step + first; v < g.n; v += tt * step) {
+        const int r = parent[v];
+        if (ROOTS && r != v) continue;
+        const int b = g.srow[v], deg = g.srow[v + 1] - b;
+        int x[K], least = r;
+#pragma unroll
+        for (int k = 0; k < K; ++k) x[k] = k < deg ? g.scol[b + k] : (int)v;
+#pragma unroll
+        for (int k = 0; k < K; ++k) x[k] = parent[x[k]];
+#pragma unroll
+        for (int k = 0; k < K; ++k) least = min(least, x[k]);
+        if (least < r && (ROOTS || parent[r] == r)) {
+            parent[r] = least;
+            hooked = true;
+        }
+    }
+    return hooked;
+}
+
 __global__ __launch_bounds__(256) void k_uf(Round R) {
     if (!round_begin(R)) return;
     const DevGraph& g = R.g;
@@ -2572,6 +2602,9 @@ __global__ __launch_bounds__(256) void k_uf(Round R) {
                 acc.u++;
             }
         }
+    } else if (R.r == 1) {
+        const bool hooked = uf_hook<true>(R, 1, 0);
+        if (__syncthreads_or(hooked) && threadIdx.x == 0) R.ws.ctl->hooked[0] = 1;
     } else if (R.r == 2) {
         // the giant component's root: the most frequent root of 1024
         // vertices spread over the ids (a multiplicative hash of i), counted
@@ -2665,40 +2698,17 @@ __global__ __launch_bounds__(256) void k_uf_long(Round R) {
     block_finish(R, acc, R.r % 3, KIND_AUX);
 }
 
-// Round 1, pass `pass`.  Pass 0: every root takes the smallest parent that its
-// first neighbours have.  The roots it leaves have mostly neighbours of their
+// Round 1, pass `pass`.  Pass 0 (k_uf): every root takes the smallest parent that
+// its first neighbours have.  The roots it leaves have mostly neighbours of their
 // own tree, so the later passes look from one vertex in `share` (another
 // each pass), which hooks its parent if that is a root.  Several
 // vertices may hook one root; the last store stands, and a join that is lost
 // so is found again in round 3 unless both its trees are in the giant one.
 // After a pass from the vertices that hooked nothing the rest return at once.
-template <bool ROOTS>
-__global__ __launch_bounds__(256) void k_uf_hook(Round R, int pass, int share, int first) {
+__global__ __launch_bounds__(256) void k_uf_hook(Round R, int pass, int share) {
     Ctl* ctl = R.ws.ctl;
     if (*(volatile int*)&ctl->done || (pass > 1 && !*(volatile int*)&ctl->hooked[pass - 1])) return;
-    const DevGraph& g = R.g;
-    bool hooked = false;
-    int* parent = R.val;
-    constexpr int K = ROOTS ? kUfFirst : kUfFirst / 2;
-    const long long step = ROOTS ? 1 : share;
-    const long long tid = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    const long long tt = (long long)gridDim.x * blockDim.x;
-    for (long long v = tid * step + first; v < g.n; v += tt * step) {
-        const int r = parent[v];
-        if (ROOTS && r != v) continue;
-        const int b = g.srow[v], deg = g.srow[v + 1] - b;
-        int x[K], least = r;
-#pragma unroll
-        for (int k = 0; k < K; ++k) x[k] = k < deg ? g.scol[b + k] : (int)v;
-#pragma unroll
-        for (int k = 0; k < K; ++k) x[k] = parent[x[k]];
-#pragma unroll
-        for (int k = 0; k < K; ++k) least = min(least, x[k]);
-        if (least < r && (ROOTS || parent[r] == r)) {
-            parent[r] = least;
-            hooked = true;
-        }
-    }
+    const bool hooked = uf_hook<false>(R, share, (pass - 1) % share);
     if (__syncthreads_or(hooked) && threadIdx.x == 0) ctl->hooked[pass] = 1;
 }
 
@@ -3001,8 +3011,7 @@ hipError_t launch_uf(const Round& R, int grid, int block, hipStream_t s) {
 
 hipError_t launch_uf_hook(const Round& R, int pass, int share, int grid, int block,
                           hipStream_t s) {
-    if (pass == 0) GG_LAUNCH(k_uf_hook<true>, grid, block, s, R, pass, 1, 0);
-    GG_LAUNCH(k_uf_hook<false>, grid, block, s, R, pass, share, (pass - 1) % share);
+    GG_LAUNCH(k_uf_hook, grid, block, s, R, pass, share);
 }
 
 hipError_t launch_uf_long(const Round& R, int grid, int block, hipStream_t s) {
