@@ -2143,9 +2143,10 @@ __global__ __launch_bounds__(kSmallBlock) void k_small(Round R) {
         rounds = max(rounds, r + 1);
         for (int v = threadIdx.x; v < n; v += kSmallBlock) R.val[base + v] = dist[v];
         // the next instance that no workgroup has taken
-        if (R.inst && threadIdx.x == 0) s_next = gridDim.x + atomicAdd(&R.ws.ctl->taken, 1);
+        const bool more = count > (int)gridDim.x;
+        if (more && threadIdx.x == 0) s_next = gridDim.x + atomicAdd(&R.ws.ctl->taken, 1);
         __syncthreads();
-        i = R.inst ? s_next : count;
+        i = more ? s_next : count;
     }
     small_finish(R, acc, rounds);
 }
