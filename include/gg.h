@@ -40,7 +40,10 @@
  *     forms (gg_sssp_async and below) return at once with a ticket; one host
  *     thread can so keep several traversals in flight together.
  *   - A HIP failure is reported as GG_EHIP and recorded on the graph handle;
- *     gg_graph_error() returns the first recorded failure.
+ *     gg_graph_error() returns the first recorded failure.  A plain call
+ *     spins while its rounds report every 0.2 ms or sooner; while they do not,
+ *     it yields the core, sleeps, and asks the stream for a failure every
+ *     millisecond.
  */
 #ifndef GG_H
 #define GG_H
